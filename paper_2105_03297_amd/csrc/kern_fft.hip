@@ -2024,8 +2024,10 @@ int first_t(const feh_plan &p, const FftArgs &fa, int mode) {
     // tuned value, never below a quarter of the default: the partial-sum
     // buffer holds one slot per pencil block for that size
     if (p.tune_pb_first > 0 && p.tune_pb_first < PB) PB = std::max(p.tune_pb_first, std::max(1, PB / 4));
+    // the compile-time pass reads the table in blocks of its own size, also on
+    // a grid with fewer pencils than one block
     if (ctpb > 0) PB = ctpb;
-    if (PB > a.inner_total) PB = (int)a.inner_total;
+    else if (PB > a.inner_total) PB = (int)a.inner_total;
     a.PB = PB;
     a.d_PB = FastDiv::make((uint32_t)PB);
     a.nbd = FastDiv::make((uint32_t)(PB * DIM));
