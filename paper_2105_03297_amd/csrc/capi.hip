@@ -115,6 +115,13 @@ static std::vector<std::vector<int>> radix_candidates(int n) {
     return out;
 }
 
+static size_t half_spectrum_bytes(const feh_plan &p) { return (size_t)p.L * p.dim * p.Nspec * 2 * p.rsize; }
+
+// partial sums of the CG kernels (part_stride a load case) or of the post-processing
+static size_t partial_bytes(const feh_plan &p) {
+    return std::max(p.part_stride * p.L, (size_t)post_num_slots(p) * post_num_parts(p)) * sizeof(double);
+}
+
 static void layout(feh_plan &p) {
     const size_t vec = (size_t)p.L * p.dim * p.N * p.rsize;
     size_t o = 0;
@@ -125,10 +132,10 @@ static void layout(feh_plan &p) {
     };
     p.off_u = take(vec);
     // r: a real field, or in the CG of cg_residual_spectral its last-axis half spectrum
-    p.off_r = take(std::max(vec, (size_t)p.L * p.dim * p.Nspec * 2 * p.rsize));
+    p.off_r = take(std::max(vec, half_spectrum_bytes(p)));
     p.off_p = take(vec);
     p.off_q = take(vec);
-    p.off_spec = take((size_t)p.L * p.dim * p.Nspec * 2 * p.rsize);
+    p.off_spec = take(half_spectrum_bytes(p));
     p.off_lam = take(p.nbatch * p.N * p.rsize);
     p.off_mu = take(p.nbatch * p.N * p.rsize);
     for (int a = 0; a < 3; ++a) {
@@ -153,10 +160,7 @@ static void layout(feh_plan &p) {
     }
     const int fp = (int)((inner0 + pbmin - 1) / pbmin);
     p.part_stride = (size_t)(sp > fp ? sp : fp);
-    size_t parts = p.part_stride * p.L;
-    const size_t post_parts = (size_t)post_num_slots(p) * post_num_parts(p);
-    if (post_parts > parts) parts = post_parts;
-    p.off_part = take(parts * sizeof(double));
+    p.off_part = take(partial_bytes(p));
     p.off_state = take((size_t)p.L * sizeof(LcState));
     p.off_flag = take(256);
     // sensitivity pair list: l, m (int), group offsets (2 kMaxLoad ints, keeps the
@@ -170,6 +174,50 @@ static void layout(feh_plan &p) {
         p.off_minv = take(ncomp * (size_t)(inner0 + 32) * (size_t)p.n[0] * p.rsize);
     }
     p.total = o;
+}
+
+NodalWork nodal_layout(const feh_plan &p) {
+    const size_t nodal = (size_t)p.L * p.dim * p.N;
+    NodalWork w{};
+    size_t o = 0;
+    auto take = [&](size_t bytes) {
+        const size_t at = o;
+        o = align256(o + bytes);
+        return at;
+    };
+    w.u = take(nodal * sizeof(double));
+    w.r = take(std::max(nodal * p.rsize, half_spectrum_bytes(p)));
+    w.p = take(nodal * p.rsize);
+    w.q = take(nodal * p.rsize);
+    w.spec = take(half_spectrum_bytes(p));
+    w.ebar = take((size_t)p.L * 9 * sizeof(double));
+    w.sums = take((size_t)post_num_slots(p) * sizeof(double));
+    w.part = take(partial_bytes(p));
+    w.state = take((size_t)p.L * sizeof(LcState));
+    w.total = o;
+    return w;
+}
+
+NodalScope::NodalScope(feh_plan &p, char *work, const NodalWork &w) : p_(p), solved_(p.solved), prof_(p.prof_on) {
+    // the launchers address every buffer from the plan's workspace: offsets to
+    // the other buffer, modulo 2^64
+    const size_t to = reinterpret_cast<uintptr_t>(work) - reinterpret_cast<uintptr_t>(p.ws);
+    size_t *const at[9] = {&p.off_u, &p.off_r, &p.off_p, &p.off_q, &p.off_spec, &p.off_ebar, &p.off_sums, &p.off_part, &p.off_state};
+    const size_t in[9] = {w.u, w.r, w.p, w.q, w.spec, w.ebar, w.sums, w.part, w.state};
+    for (int i = 0; i < 9; ++i) {
+        off_[i] = *at[i];
+        *at[i] = to + in[i];
+    }
+    p.u_f64 = true;
+    p.prof_on = false;
+}
+
+NodalScope::~NodalScope() {
+    size_t *const at[9] = {&p_.off_u, &p_.off_r, &p_.off_p, &p_.off_q, &p_.off_spec, &p_.off_ebar, &p_.off_sums, &p_.off_part, &p_.off_state};
+    for (int i = 0; i < 9; ++i) *at[i] = off_[i];
+    p_.u_f64 = false;
+    p_.prof_on = prof_;
+    p_.solved = solved_;
 }
 
 // e^{+2 pi i j / n} with the symmetries of the circle applied exactly: the
@@ -357,6 +405,7 @@ static int cg_iteration(const feh_plan &p, LcState *st, double tol, int max_iter
     fa.spec = p.ws + p.off_spec;
     fa.p_upd = p.ws + p.off_p;
     fa.u_upd = p.ws + p.off_u;
+    fa.u_f64 = p.u_f64;
     fa.partial = part;
     fa.state = st;
     fa.out_scale = 1.0 / (double)p.N;
@@ -686,7 +735,8 @@ static int solve_begin(feh_plan &p, const double *Ebar_host, double tol, int max
         CK(launch_finish_rho(p, st, part, first_num_parts(p), 0, tol, max_iter));
         sa.in0 = p.ws + p.off_u;
     } else {
-        CK(launch_fill(p, p.ws + p.off_u, nvec, 0.0));
+        // all-zero bits are zero in either type u may have
+        CK(launch_fill(p, p.ws + p.off_u, p.u_f64 ? nvec * 8 / p.rsize : nvec, 0.0));
         sa.in0 = nullptr;
     }
     // r = f - K u0, first search direction p = M^+ r; with the residual kept
@@ -798,6 +848,16 @@ static int solve_all(feh_plan &p, const double *Ebar_host, double tol, int max_i
     }
     return solve_end(p, u_dev, strain_dev, stress_dev, stress_mean_host, energy_host, report_host);
 }
+
+}  // extern "C"
+
+int feh::nodal_solve(feh_plan &p, const double *Ebar_host, double tol, int max_iter, void *strain_dev,
+                     double *stress_mean_host, double *energy_host, feh_report *report_host) {
+    return solve_all(p, Ebar_host, tol, max_iter, nullptr, nullptr, strain_dev, nullptr, stress_mean_host, energy_host,
+                     report_host);
+}
+
+extern "C" {
 
 int feh_solve(feh_plan *plan, const double *Ebar_host, double tol, int max_iter, const void *u0_dev, void *u_dev,
               void *strain_dev, void *stress_dev, double *stress_mean_host, double *energy_host,

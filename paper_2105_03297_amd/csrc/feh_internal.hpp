@@ -151,6 +151,7 @@ struct feh_plan {
     int tune_first_perlc = 0;           // axis-0 pass: 1 one workgroup per load case, -1 all load cases, 0 default
     int tune_ct = 1;                    // 1: compile-time transforms where the shape has one, 0: run-time passes only
     bool solved = false;                // off_u holds the fluctuations of the last feh_solve
+    bool u_f64 = false;                 // off_u holds doubles whatever prec (set while a NodalScope is in place)
     // the (B^*B)^-1 table at off_minv: built for this workspace and pencil
     // block size (0: not built); rebuilt by the first-axis launcher on change
     mutable const char *minv_ws = nullptr;
@@ -237,6 +238,7 @@ struct FftArgs {
     void *z = nullptr;           // real output
     void *p_upd = nullptr;       // CG update fused into the last inverse pass (nullable):
     void *u_upd = nullptr;       //   u += alpha_pend p, then p = z + beta p, in place (z not stored)
+    bool u_f64 = false;          // u_upd is kept in double whatever the plan precision
     double *partial = nullptr;   // Parseval r.z partials
     const LcState *state = nullptr;  // active mask, alpha (nullable: all active, no axpy)
     double out_scale = 1.0;      // c2r output scale
@@ -269,7 +271,7 @@ int launch_finish_pq(const feh_plan &p, LcState *st, const double *partial, int 
 int launch_finish_rho_stride(const feh_plan &p, LcState *st, const double *partial, int nparts, int stride,
                              int mode, double tol, int max_iter);
 int launch_finish_pq_stride(const feh_plan &p, LcState *st, const double *partial, int nparts, int stride);
-int launch_finalize_u(const feh_plan &p, void *u, const void *pv, const LcState *st);
+int launch_finalize_u(const feh_plan &p, void *u, const void *pv, const LcState *st);  // u in double with p.u_f64
 int launch_material_lame(const feh_plan &p, const void *lam, const void *mu, int *flag);
 int launch_material_phases(const feh_plan &p, const int32_t *phase, const double *tab, int n_phase,
                            int *flag);
@@ -291,6 +293,32 @@ int launch_sensitivity(const feh_plan &p, const void *u, const double *Ebar_dev,
                        const double *pw, const int *gofs, bool offdiag, void *g_lam, void *g_mu, void *g_E,
                        double aE, double bE);
 int post_num_slots(const feh_plan &p);
+
+// Solve of the factored nodal form on vectors outside the plan's workspace
+// (capi.hip).  NodalWork: byte offsets of those vectors in a caller's buffer;
+// u is in double whatever the plan precision.
+struct NodalWork {
+    size_t u, r, p, q, spec, ebar, sums, part, state, total;
+};
+NodalWork nodal_layout(const feh_plan &p);
+// While alive, the plan's vectors, CG state and partial sums are those in
+// `work` (its material and tables stay its own); afterwards everything,
+// the last solution included, is as it was.
+class NodalScope {
+public:
+    NodalScope(feh_plan &p, char *work, const NodalWork &w);
+    ~NodalScope();
+    NodalScope(const NodalScope &) = delete;
+    NodalScope &operator=(const NodalScope &) = delete;
+
+private:
+    feh_plan &p_;
+    size_t off_[9];
+    bool solved_, prof_;
+};
+// every load case to the tolerance from u = 0: outputs as feh_solve
+int nodal_solve(feh_plan &p, const double *Ebar_host, double tol, int max_iter, void *strain_dev,
+                double *stress_mean_host, double *energy_host, feh_report *report_host);
 
 // partial-sum sizes
 int stencil_num_parts(const feh_plan &p);

@@ -135,13 +135,13 @@ __global__ void k_finish_pq(LcState *st, const double *part, int nparts, int str
 
 // u += alpha_pend * p for every load case (the update still pending when a
 // load case stopped), then clear the pending step.
-template <typename T>
-__global__ void k_finalize_u(T *u, const T *p, const LcState *st, long long per_lc, int L) {
+template <typename T, typename U = T>
+__global__ void k_finalize_u(U *u, const T *p, const LcState *st, long long per_lc, int L) {
     const long long total = per_lc * L;
     for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < total; i += (long long)gridDim.x * blockDim.x) {
         const int l = (int)(i / per_lc);
         const double a = st[l].alpha_pend;
-        if (a != 0.0) u[i] += T(a) * p[i];
+        if (a != 0.0) u[i] += U(a) * U(p[i]);
     }
 }
 
@@ -345,6 +345,9 @@ int launch_finalize_u(const feh_plan &p, void *u, const void *pv, const LcState 
     if (p.prec == FEH_FP64)
         hipLaunchKernelGGL(k_finalize_u<double>, dim3(g), dim3(kThreads), 0, p.stream, (double *)u, (const double *)pv,
                            st, per, p.L);
+    else if (p.u_f64)
+        hipLaunchKernelGGL((k_finalize_u<float, double>), dim3(g), dim3(kThreads), 0, p.stream, (double *)u,
+                           (const float *)pv, st, per, p.L);
     else
         hipLaunchKernelGGL(k_finalize_u<float>, dim3(g), dim3(kThreads), 0, p.stream, (float *)u, (const float *)pv,
                            st, per, p.L);

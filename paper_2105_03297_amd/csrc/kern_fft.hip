@@ -367,7 +367,7 @@ struct FK {
     const Cx<T> *spec_in;     // middle pass: read from here, write spec (null: in place)
     T *z;
     T *p_upd;                 // fused CG update in the last inverse pass
-    T *u_upd;
+    void *u_upd;              // T, or double in the accumulating variant (U of the kernels)
     double *partial;
     const LcState *st;
     const Cx<T> *tw;          // twiddles of the transformed axis (full length)
@@ -674,9 +674,11 @@ __global__ __launch_bounds__(kFftThreads) __attribute__((amdgpu_waves_per_eu(kGe
 // ---------------------------------------------------------------------------
 // last axis, half spectrum -> real (times out_scale).  UPD: the real result z
 // is not stored; instead the CG update u += alpha_pend p, p = z + beta p is
-// applied in place (one pass over p and u while z is in registers).
+// applied in place (one pass over p and u while z is in registers).  U: the
+// type u is kept in (T, or double in an FP32 plan whose caller differentiates
+// u and must not lose the digits that its rounding to float would take).
 // ---------------------------------------------------------------------------
-template <typename T, int PPT, bool GEN, bool UPD>
+template <typename T, int PPT, bool GEN, bool UPD, typename U = T>
 __global__ __launch_bounds__(kFftThreads) __attribute__((amdgpu_waves_per_eu(kGenWaves<T, GEN>))) void k_last_inv(FK<T> a) {
     constexpr int NT = kFftThreads;
     __shared__ Cx<T> sbuf[GEN ? 1 : PPT * NT];
@@ -762,11 +764,14 @@ __global__ __launch_bounds__(kFftThreads) __attribute__((amdgpu_waves_per_eu(kGe
     }
     const long long lbase = (long long)lc * D * N + s0 * a.nlast;
     if constexpr (UPD) {
-        const T beta = T(a.st[lc].beta), ap = T(a.st[lc].alpha_pend);
+        const T beta = T(a.st[lc].beta);
+        const U ap = U(a.st[lc].alpha_pend);
+        U *uu = static_cast<U *>(a.u_upd);
         constexpr int CH = 8;  // slots per round: two loads each in flight
         #pragma unroll
         for (int h = 0; h < PPT; h += CH) {
-            Cx<T> pv[CH], uv[CH];
+            Cx<T> pv[CH];
+            Cx<U> uv[CH];
             #pragma unroll
             for (int k = 0; k < CH; ++k) {
                 const int e0 = threadIdx.x + (h + k) * NT;
@@ -779,10 +784,10 @@ __global__ __launch_bounds__(kFftThreads) __attribute__((amdgpu_waves_per_eu(kGe
                 const long long o = lbase + (long long)c * N + (long long)sl * a.nlast + (even ? 2 * j : j);
                 if (even) {
                     pv[k] = ldc_nt(reinterpret_cast<const Cx<T> *>(a.p_upd + o));
-                    uv[k] = ldc_nt(reinterpret_cast<const Cx<T> *>(a.u_upd + o));
+                    uv[k] = ldc_nt(reinterpret_cast<const Cx<U> *>(uu + o));
                 } else {
                     pv[k] = Cx<T>{ldr_nt(a.p_upd + o), T(0)};
-                    uv[k] = Cx<T>{ldr_nt(a.u_upd + o), T(0)};
+                    uv[k] = Cx<U>{ldr_nt(uu + o), U(0)};
                 }
             }
             #pragma unroll
@@ -795,13 +800,13 @@ __global__ __launch_bounds__(kFftThreads) __attribute__((amdgpu_waves_per_eu(kGe
                 if (e0 < cnt && sl < nrows) {
                     const long long o = lbase + (long long)c * N + (long long)sl * a.nlast + (even ? 2 * j : j);
                     const Cx<T> z = {y[h + k].x * sc, y[h + k].y * sc};
-                    const Cx<T> un = {uv[k].x + ap * pv[k].x, uv[k].y + ap * pv[k].y};
+                    const Cx<U> un = {uv[k].x + ap * U(pv[k].x), uv[k].y + ap * U(pv[k].y)};
                     const Cx<T> pn = {z.x + beta * pv[k].x, z.y + beta * pv[k].y};
                     if (even) {
-                        stc_nt(reinterpret_cast<Cx<T> *>(a.u_upd + o), un);
+                        stc_nt(reinterpret_cast<Cx<U> *>(uu + o), un);
                         stc_nt(reinterpret_cast<Cx<T> *>(a.p_upd + o), pn);
                     } else {
-                        str_nt(a.u_upd + o, un.x);
+                        str_nt(uu + o, un.x);
                         str_nt(a.p_upd + o, pn.x);
                     }
                 }
@@ -971,7 +976,7 @@ __global__ __launch_bounds__(kFftThreads) void k_last_fwd_ct(FK<T> a) {
     else last_fwd_ct_body<T, NL, D, MODE, false>(a, lc, s0, nrows, alpha, buf, twl);
 }
 
-template <typename T, int NL, int D, bool UPD, bool FULL>
+template <typename T, int NL, int D, bool UPD, bool FULL, typename U>
 __device__ __forceinline__ void last_inv_ct_body(const FK<T> &a, int lc, long long s0, int nrows, Cx<T> *buf,
                                                  const Cx<T> *twl) {
     constexpr int NT = kFftThreads, NC = NL / 2, NH = NC + 1;
@@ -1027,12 +1032,20 @@ __device__ __forceinline__ void last_inv_ct_body(const FK<T> &a, int lc, long lo
     const unsigned N32 = (unsigned)a.N, row0 = (unsigned)(s0 * NL);
     if constexpr (UPD) {
         Cx<T> *pl = reinterpret_cast<Cx<T> *>(a.p_upd + lbase);
-        Cx<T> *ul = reinterpret_cast<Cx<T> *>(a.u_upd + lbase);
-        const T beta = T(a.st[lc].beta), ap = T(a.st[lc].alpha_pend);
+        // u's pairs at the element offsets of p's (in bytes when it has p's type,
+        // else through a 64-bit index: its byte offsets may pass 32 bits)
+        Cx<U> *ul = reinterpret_cast<Cx<U> *>(static_cast<U *>(a.u_upd) + lbase);
+        auto u_at = [&](unsigned o) {
+            if constexpr (sizeof(U) == sizeof(T)) return at_byte(ul, o);
+            else return ul + o / (unsigned)sizeof(Cx<T>);
+        };
+        const T beta = T(a.st[lc].beta);
+        const U ap = U(a.st[lc].alpha_pend);
         constexpr int CH2 = 8;  // slots per round: two loads each in flight
         #pragma unroll
         for (int h = 0; h < PPT; h += CH2) {
-            Cx<T> pv[CH2], uv[CH2];
+            Cx<T> pv[CH2];
+            Cx<U> uv[CH2];
             #pragma unroll
             for (int k = 0; k < CH2; ++k) {
                 const int e = threadIdx.x + (h + k) * NT;
@@ -1041,7 +1054,7 @@ __device__ __forceinline__ void last_inv_ct_body(const FK<T> &a, int lc, long lo
                 const int sl = (FULL || sl0 < nrows) ? sl0 : nrows - 1;
                 const unsigned o = last_pair_offset<T, NL, D>(c, sl, j, N32, row0);
                 pv[k] = ldc_nt(at_byte(pl, o));
-                uv[k] = ldc_nt(at_byte(ul, o));
+                uv[k] = ldc_nt(u_at(o));
             }
             #pragma unroll
             for (int k = 0; k < CH2; ++k) {
@@ -1051,9 +1064,9 @@ __device__ __forceinline__ void last_inv_ct_body(const FK<T> &a, int lc, long lo
                 if (FULL || sl < nrows) {
                     const unsigned o = last_pair_offset<T, NL, D>(c, sl, j, N32, row0);
                     const Cx<T> z = {y[h + k].x * sc, y[h + k].y * sc};
-                    const Cx<T> un = {uv[k].x + ap * pv[k].x, uv[k].y + ap * pv[k].y};
+                    const Cx<U> un = {uv[k].x + ap * U(pv[k].x), uv[k].y + ap * U(pv[k].y)};
                     const Cx<T> pn = {z.x + beta * pv[k].x, z.y + beta * pv[k].y};
-                    stc_nt(at_byte(ul, o), un);
+                    stc_nt(u_at(o), un);
                     stc_nt(at_byte(pl, o), pn);
                 }
             }
@@ -1071,7 +1084,7 @@ __device__ __forceinline__ void last_inv_ct_body(const FK<T> &a, int lc, long lo
     }
 }
 
-template <typename T, int NL, int D, bool UPD>
+template <typename T, int NL, int D, bool UPD, typename U = T>
 __global__ __launch_bounds__(kFftThreads) void k_last_inv_ct(FK<T> a) {
     constexpr int NT = kFftThreads, NC = NL / 2;
     constexpr int RR = ct_last_rows<NL, D>(), NB = D * RR;
@@ -1086,8 +1099,8 @@ __global__ __launch_bounds__(kFftThreads) void k_last_inv_ct(FK<T> a) {
     const int nrows = (int)min((long long)RR, a.rows - s0);
     for (int i = threadIdx.x; i < NL; i += NT) twl[i] = a.tw_last[i];
     __syncthreads();
-    if (nrows == RR) last_inv_ct_body<T, NL, D, UPD, true>(a, lc, s0, nrows, buf, twl);
-    else last_inv_ct_body<T, NL, D, UPD, false>(a, lc, s0, nrows, buf, twl);
+    if (nrows == RR) last_inv_ct_body<T, NL, D, UPD, true, U>(a, lc, s0, nrows, buf, twl);
+    else last_inv_ct_body<T, NL, D, UPD, false, U>(a, lc, s0, nrows, buf, twl);
 }
 
 // ---------------------------------------------------------------------------
@@ -1764,7 +1777,7 @@ FK<T> base_args(const feh_plan &p, const FftArgs &fa) {
     a.spec_in = static_cast<const Cx<T> *>(fa.spec_in);
     a.z = static_cast<T *>(fa.z);
     a.p_upd = static_cast<T *>(fa.p_upd);
-    a.u_upd = static_cast<T *>(fa.u_upd);
+    a.u_upd = fa.u_upd;
     a.partial = fa.partial;
     a.st = fa.state;
     a.dim = p.dim;
@@ -1874,7 +1887,9 @@ int last_t(const feh_plan &p, const FftArgs &fa, bool inverse) {
 #define FEH_LAST_CT(NLv, Dv)                                                                                    \
         do {                                                                                                      \
             if (inverse) {                                                                                        \
-                if (upd) hipLaunchKernelGGL((k_last_inv_ct<T, NLv, Dv, true>), g, b, 0, p.stream, a);             \
+                if (upd && fa.u_f64)                                                                              \
+                    hipLaunchKernelGGL((k_last_inv_ct<T, NLv, Dv, true, double>), g, b, 0, p.stream, a);          \
+                else if (upd) hipLaunchKernelGGL((k_last_inv_ct<T, NLv, Dv, true>), g, b, 0, p.stream, a);        \
                 else hipLaunchKernelGGL((k_last_inv_ct<T, NLv, Dv, false>), g, b, 0, p.stream, a);                \
             } else {                                                                                              \
                 if (a.use_axpy == 2) hipLaunchKernelGGL((k_last_fwd_ct<T, NLv, Dv, 2>), g, b, 0, p.stream, a);    \
@@ -1904,7 +1919,10 @@ int last_t(const feh_plan &p, const FftArgs &fa, bool inverse) {
         const bool upd = fa.p_upd != nullptr;
         if (upd && (fa.u_upd == nullptr || fa.state == nullptr))
             return set_error(FEH_EINVAL, "fused CG update needs p, u and the CG state");
-        if (upd) {
+        if (upd && fa.u_f64) {
+            if (gen) hipLaunchKernelGGL((k_last_inv<T, PPT, true, true, double>), g, b, dyn, p.stream, a);
+            else hipLaunchKernelGGL((k_last_inv<T, PPT, false, true, double>), g, b, dyn, p.stream, a);
+        } else if (upd) {
             if (gen) hipLaunchKernelGGL((k_last_inv<T, PPT, true, true>), g, b, dyn, p.stream, a);
             else hipLaunchKernelGGL((k_last_inv<T, PPT, false, true>), g, b, dyn, p.stream, a);
         } else {

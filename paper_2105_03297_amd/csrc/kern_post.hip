@@ -62,14 +62,16 @@ __device__ __forceinline__ void strains2(const T (&P)[4][2], const T (&ih)[3], d
     e[1][2] = 0.5 * (G[0][1] + G[1][0]);
 }
 
-template <typename T>
+// T: the type u is kept in; S: the plan precision of the material and the
+// fields written.
+template <typename T, typename S = T>
 struct PK {
     const T *u;         // SoA [L][D][N], may be null (zero fluctuation)
     const double *Ebar; // [L][D][D]
-    const T *lam;
-    const T *mu;
-    T *strain;          // [L][N][ne][D][D] or null
-    T *stress;
+    const S *lam;
+    const S *mu;
+    S *strain;          // [L][N][ne][D][D] or null
+    S *stress;
     double *partial;    // [slot][nblk]
     int n0, n1, n2;     // 2D: n1 = 1, n2 = n[1]
     long long N;
@@ -106,8 +108,8 @@ __device__ __forceinline__ void corner_offsets(int n0, int n1, int n2, long long
     }
 }
 
-template <typename T, int DIM>
-__device__ __forceinline__ void load_corners(const PK<T> &a, int l, const uint32_t (&idx)[1 << DIM],
+template <typename T, int DIM, typename S>
+__device__ __forceinline__ void load_corners(const PK<T, S> &a, int l, const uint32_t (&idx)[1 << DIM],
                                              T (&P)[1 << DIM][DIM]) {
     const T *ub = a.u + (long long)l * DIM * a.N;
     #pragma unroll
@@ -117,8 +119,8 @@ __device__ __forceinline__ void load_corners(const PK<T> &a, int l, const uint32
     }
 }
 
-template <typename T, int DIM>
-__device__ __forceinline__ void voxel_strains(const PK<T> &a, int l, const uint32_t (&cidx)[1 << DIM], bool add_ebar,
+template <typename T, int DIM, typename S>
+__device__ __forceinline__ void voxel_strains(const PK<T, S> &a, int l, const uint32_t (&cidx)[1 << DIM], bool add_ebar,
                                               double (&e)[DIM == 3 ? 6 : 2][DIM == 3 ? 6 : 3]) {
     T P[1 << DIM][DIM];
     load_corners<T, DIM>(a, l, cidx, P);
@@ -183,8 +185,8 @@ __device__ __forceinline__ void put_full(T *dst, const double *s) {
     }
 }
 
-template <typename T, int DIM>
-__global__ __launch_bounds__(kThreads) void k_post(PK<T> a) {
+template <typename T, int DIM, typename S = T>
+__global__ __launch_bounds__(kThreads) void k_post(PK<T, S> a) {
     constexpr int NE = DIM == 3 ? 6 : 2;
     constexpr int NS = DIM == 3 ? 6 : 3;
     __shared__ double red[kThreads / 64];
@@ -223,8 +225,8 @@ __global__ __launch_bounds__(kThreads) void k_post(PK<T> a) {
                 #pragma unroll
                 for (int k = 0; k < NS; ++k) acc[k] += s[k];
                 const long long off = (((long long)l * a.N + v) * NE + t) * DIM * DIM;
-                if (a.strain) put_full<T, DIM>(a.strain + off, e[t]);
-                if (a.stress) put_full<T, DIM>(a.stress + off, s);
+                if (a.strain) put_full<S, DIM>(a.strain + off, e[t]);
+                if (a.stress) put_full<S, DIM>(a.stress + off, s);
             }
         } else {
             double f[NE][NS];
@@ -383,8 +385,8 @@ struct ColumnCorners {
 
 // Corner values of load case l of the voxel between node planes at offsets
 // xa (cx = 0) and xb (cx = 1).
-template <typename T, int DIM>
-__device__ __forceinline__ void column_corners(const PK<T> &a, int l, uint32_t xa, uint32_t xb,
+template <typename T, int DIM, typename S>
+__device__ __forceinline__ void column_corners(const PK<T, S> &a, int l, uint32_t xa, uint32_t xb,
                                                const ColumnCorners<DIM> &cc, T (&P)[1 << DIM][DIM]) {
     #pragma unroll
     for (int i = 0; i < DIM; ++i) {
@@ -492,11 +494,11 @@ __device__ __forceinline__ void pair_sums(const T (&Pe)[1 << DIM][DIM], const T 
 // sum_elements f : s = sum_c P'[c] . F[c] + Ebar' : ss for the strains f of
 // any other corner values P' and mean strain Ebar'), and, when FIELDS, the
 // full strain and stress blocks of element TT at fe + TT D^2, fs + TT D^2.
-template <typename T, int DIM, bool FIELDS, int TT = 0>
+template <typename T, int DIM, bool FIELDS, typename S, int TT = 0>
 __device__ __forceinline__ void element_forces(const T (&P)[1 << DIM][DIM], const T (&ih)[3],
                                                const double (&Eb)[DIM][DIM], double lam, double mu,
                                                double (&F)[1 << DIM][DIM], double (&ss)[DIM == 3 ? 6 : 3], double &w,
-                                               T *fe, T *fs) {
+                                               S *fe, S *fs) {
     constexpr int NEL = DIM == 3 ? 6 : 2;
     constexpr int NS = DIM == 3 ? 6 : 3;
     if constexpr (TT < NEL) {
@@ -521,8 +523,8 @@ __device__ __forceinline__ void element_forces(const T (&P)[1 << DIM][DIM], cons
             w = fma(o2, sr[5], w);
             if constexpr (FIELDS) {
                 const double e[6] = {g[0][0], g[1][1], g[2][2], 0.5 * o0, 0.5 * o1, 0.5 * o2};
-                if (fe) put_full<T, DIM>(fe + TT * 9, e);
-                if (fs) put_full<T, DIM>(fs + TT * 9, sr);
+                if (fe) put_full<S, DIM>(fe + TT * 9, e);
+                if (fs) put_full<S, DIM>(fs + TT * 9, sr);
             }
         } else {
             const double lt = lam * (g[0][0] + g[1][1]);
@@ -535,8 +537,8 @@ __device__ __forceinline__ void element_forces(const T (&P)[1 << DIM][DIM], cons
             w = fma(o2, sr[2], w);
             if constexpr (FIELDS) {
                 const double e[3] = {g[0][0], g[1][1], 0.5 * o2};
-                if (fe) put_full<T, DIM>(fe + TT * 4, e);
-                if (fs) put_full<T, DIM>(fs + TT * 4, sr);
+                if (fe) put_full<S, DIM>(fe + TT * 4, e);
+                if (fs) put_full<S, DIM>(fs + TT * 4, sr);
             }
         }
         #pragma unroll
@@ -558,7 +560,7 @@ __device__ __forceinline__ void element_forces(const T (&P)[1 << DIM][DIM], cons
                 F[c0][i] -= f;
             }
         }
-        element_forces<T, DIM, FIELDS, TT + 1>(P, ih, Eb, lam, mu, F, ss, w, fe, fs);
+        element_forces<T, DIM, FIELDS, S, TT + 1>(P, ih, Eb, lam, mu, F, ss, w, fe, fs);
     }
 }
 
@@ -567,8 +569,8 @@ __device__ __forceinline__ void element_forces(const T (&P)[1 << DIM][DIM], cons
 // fields of load case l when requested.  The stresses of the voxel's elements
 // under load case l stay in registers while the later load cases' strains
 // are formed against them.
-template <typename T, int DIM, bool FIELDS>
-__global__ __launch_bounds__(kThreads) void k_post_march(PK<T> a, MarchGeom geo) {
+template <typename T, int DIM, bool FIELDS, typename S = T>
+__global__ __launch_bounds__(kThreads) void k_post_march(PK<T, S> a, MarchGeom geo) {
     using TL = MTile<DIM>;
     constexpr int NEL = DIM == 3 ? 6 : 2;
     constexpr int NS = DIM == 3 ? 6 : 3;
@@ -619,10 +621,10 @@ __global__ __launch_bounds__(kThreads) void k_post_march(PK<T> a, MarchGeom geo)
             for (int k = 0; k < NS; ++k) ss[k] = 0.0;
             if constexpr (FIELDS) {
                 const long long off = ((long long)l * a.N + v) * NEL * DIM * DIM;
-                element_forces<T, DIM, true>(P, a.ih, Ebl, lam, mu, F, ss, w[0], a.strain ? a.strain + off : nullptr,
-                                             a.stress ? a.stress + off : nullptr);
+                element_forces<T, DIM, true, S>(P, a.ih, Ebl, lam, mu, F, ss, w[0], a.strain ? a.strain + off : nullptr,
+                                                a.stress ? a.stress + off : nullptr);
             } else {
-                element_forces<T, DIM, false>(P, a.ih, Ebl, lam, mu, F, ss, w[0], nullptr, nullptr);
+                element_forces<T, DIM, false, S>(P, a.ih, Ebl, lam, mu, F, ss, w[0], nullptr, nullptr);
             }
             #pragma unroll
             for (int k = 0; k < NS; ++k) sig[k] += ss[k];
@@ -811,11 +813,11 @@ __global__ void k_reduce_slots(const double *part, int nblk, double *out, double
     if (threadIdx.x == 0) out[slot] = s * scale;
 }
 
-template <typename T>
-PK<T> post_args(const feh_plan &p) {
-    PK<T> a{};
-    a.lam = p.ptr<const T>(p.off_lam);
-    a.mu = p.ptr<const T>(p.off_mu);
+template <typename T, typename S = T>
+PK<T, S> post_args(const feh_plan &p) {
+    PK<T, S> a{};
+    a.lam = p.ptr<const S>(p.off_lam);
+    a.mu = p.ptr<const S>(p.off_mu);
     if (p.dim == 3) {
         a.n0 = (int)p.n[0];
         a.n1 = (int)p.n[1];
@@ -858,14 +860,14 @@ int post_num_slots(const feh_plan &p) {
     return p.L * ns + p.nbatch * (p.G * (p.G + 1) / 2);
 }
 
-template <typename T>
+template <typename T, typename S = T>
 static int post_t(const feh_plan &p, const void *u, const double *Ebar, void *strain, void *stress, double *partial,
                   double *sums) {
-    PK<T> a = post_args<T>(p);
+    PK<T, S> a = post_args<T, S>(p);
     a.u = static_cast<const T *>(u);
     a.Ebar = Ebar;
-    a.strain = static_cast<T *>(strain);
-    a.stress = static_cast<T *>(stress);
+    a.strain = static_cast<S *>(strain);
+    a.stress = static_cast<S *>(stress);
     a.partial = partial;
     if (march_ok(p)) {
         const MarchGeom geo = p.dim == 3 ? march_geom<3>(p) : march_geom<2>(p);
@@ -873,22 +875,22 @@ static int post_t(const feh_plan &p, const void *u, const double *Ebar, void *st
         dim3 g(a.nblk * p.G, p.nbatch);
         const bool fields = a.strain || a.stress;
         if (p.dim == 3 && fields)
-            hipLaunchKernelGGL((k_post_march<T, 3, true>), g, dim3(kThreads), 0, p.stream, a, geo);
+            hipLaunchKernelGGL((k_post_march<T, 3, true, S>), g, dim3(kThreads), 0, p.stream, a, geo);
         else if (p.dim == 3)
-            hipLaunchKernelGGL((k_post_march<T, 3, false>), g, dim3(kThreads), 0, p.stream, a, geo);
+            hipLaunchKernelGGL((k_post_march<T, 3, false, S>), g, dim3(kThreads), 0, p.stream, a, geo);
         else if (fields)
-            hipLaunchKernelGGL((k_post_march<T, 2, true>), g, dim3(kThreads), 0, p.stream, a, geo);
+            hipLaunchKernelGGL((k_post_march<T, 2, true, S>), g, dim3(kThreads), 0, p.stream, a, geo);
         else
-            hipLaunchKernelGGL((k_post_march<T, 2, false>), g, dim3(kThreads), 0, p.stream, a, geo);
+            hipLaunchKernelGGL((k_post_march<T, 2, false, S>), g, dim3(kThreads), 0, p.stream, a, geo);
     } else {
         const long long nb = (p.N + kThreads - 1) / kThreads;
         a.nblk = (int)(nb > 512 ? 512 : nb);
         const int nq = p.L + p.nbatch * (p.G * (p.G + 1) / 2);
         dim3 g(a.nblk, nq);
         if (p.dim == 3)
-            hipLaunchKernelGGL((k_post<T, 3>), g, dim3(kThreads), 0, p.stream, a);
+            hipLaunchKernelGGL((k_post<T, 3, S>), g, dim3(kThreads), 0, p.stream, a);
         else
-            hipLaunchKernelGGL((k_post<T, 2>), g, dim3(kThreads), 0, p.stream, a);
+            hipLaunchKernelGGL((k_post<T, 2, S>), g, dim3(kThreads), 0, p.stream, a);
     }
     int rc = hip_check(hipGetLastError(), "post launch");
     if (rc) return rc;
@@ -900,6 +902,7 @@ static int post_t(const feh_plan &p, const void *u, const double *Ebar, void *st
 
 int launch_post_sums(const feh_plan &p, const void *u, const double *Ebar_dev, void *strain, void *stress,
                      double *partial, double *sums) {
+    if (p.prec != FEH_FP64 && p.u_f64) return post_t<double, float>(p, u, Ebar_dev, strain, stress, partial, sums);
     return p.prec == FEH_FP64 ? post_t<double>(p, u, Ebar_dev, strain, stress, partial, sums)
                               : post_t<float>(p, u, Ebar_dev, strain, stress, partial, sums);
 }
