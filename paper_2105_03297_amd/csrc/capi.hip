@@ -198,7 +198,8 @@ NodalWork nodal_layout(const feh_plan &p) {
     return w;
 }
 
-NodalScope::NodalScope(feh_plan &p, char *work, const NodalWork &w) : p_(p), solved_(p.solved), prof_(p.prof_on) {
+NodalScope::NodalScope(feh_plan &p, char *work, const NodalWork &w)
+    : p_(p), part_stride_(p.part_stride), solved_(p.solved), prof_(p.prof_on) {
     // the launchers address every buffer from the plan's workspace: offsets to
     // the other buffer, modulo 2^64
     const size_t to = reinterpret_cast<uintptr_t>(work) - reinterpret_cast<uintptr_t>(p.ws);
@@ -215,7 +216,10 @@ NodalScope::NodalScope(feh_plan &p, char *work, const NodalWork &w) : p_(p), sol
 NodalScope::~NodalScope() {
     size_t *const at[9] = {&p_.off_u, &p_.off_r, &p_.off_p, &p_.off_q, &p_.off_spec, &p_.off_ebar, &p_.off_sums, &p_.off_part, &p_.off_state};
     for (int i = 0; i < 9; ++i) *at[i] = off_[i];
+    p_.part_stride = part_stride_;
     p_.u_f64 = false;
+    p_.metric = 0;
+    p_.op = nullptr;
     p_.prof_on = prof_;
     p_.solved = solved_;
 }
@@ -315,8 +319,8 @@ static int read_flag(feh_plan &p, int *flag_dev, const char *what) {
 // r is consumed by the first pass, so z may be the same buffer.
 // z = M^+ r.  rhat non-null (3D): the last-axis half spectrum of r is written
 // there and kept (the forward middle pass reads it into the spectrum).
-static int precondition(const feh_plan &p, const void *r, void *z, double *partial, const LcState *st,
-                        bool unit_volume, void *rhat = nullptr) {
+int precondition(const feh_plan &p, const void *r, void *z, double *partial, const LcState *st, bool unit_volume,
+                 void *rhat) {
     FftArgs fa;
     fa.unit_volume = unit_volume;
     fa.r = r;
@@ -382,7 +386,7 @@ static void prof_drain(const feh_plan &p) {
 //   last inverse pass, u += alpha p and p = z + beta p.  A load case that stops
 //   at the convergence test keeps its last u += alpha p pending (applied by
 //   the finalisation).
-static int cg_iteration(const feh_plan &p, LcState *st, double tol, int max_iter) {
+int cg_iteration(const feh_plan &p, LcState *st, double tol, int max_iter) {
     double *part = p.ptr<double>(p.off_part);
     StencilArgs sa;
     sa.in0 = p.ws + p.off_p;
@@ -392,11 +396,12 @@ static int cg_iteration(const feh_plan &p, LcState *st, double tol, int max_iter
     sa.unit_volume = true;
     {
         ProfScope ps(p, 0);
-        CK(launch_stencil(p, ST_CG, sa));
+        if (p.op) CK(launch_nodal_tangent(p, *p.op, sa.in0, sa.out0, st));
+        else CK(launch_stencil(p, ST_CG, sa));
     }
     {
         ProfScope ps(p, 1);
-        CK(launch_finish_pq(p, st, part, stencil_num_parts(p)));
+        CK(launch_finish_pq(p, st, part, p.op ? nodal_num_parts(p) : stencil_num_parts(p)));
     }
     FftArgs fa;
     fa.r = p.ws + p.off_r;

@@ -13,6 +13,8 @@
 
 namespace feh {
 
+struct NodalOp;
+
 // ---------------------------------------------------------------------------
 // complex arithmetic
 // ---------------------------------------------------------------------------
@@ -151,12 +153,17 @@ struct feh_plan {
     int tune_first_perlc = 0;           // axis-0 pass: 1 one workgroup per load case, -1 all load cases, 0 default
     int tune_ct = 1;                    // 1: compile-time transforms where the shape has one, 0: run-time passes only
     bool solved = false;                // off_u holds the fluctuations of the last feh_solve
-    bool u_f64 = false;                 // off_u holds doubles whatever prec (set while a NodalScope is in place)
+    // set while a NodalScope is in place:
+    bool u_f64 = false;                 // off_u holds doubles whatever prec
+    int metric = 0;                     // M of the preconditioner: 0 B^*B of the symmetric FE gradient, 1 + kind
+                                        // the scalar sum |D(k)|^2 of a derivative kind's full gradient
+    const feh::NodalOp *op = nullptr;   // the CG's operator (null: the stencil of kern_stencil.hip)
     // the (B^*B)^-1 table at off_minv: built for this workspace and pencil
     // block size (0: not built); rebuilt by the first-axis launcher on change
     mutable const char *minv_ws = nullptr;
     mutable int minv_pb = 0;
     mutable int minv_q = -1;            // slot interleave of the table (0: plain order)
+    mutable int minv_metric = 0;        // metric it holds
 
     // optional per-kernel event timing of the CG loop
     static constexpr int kProfKinds = 8;
@@ -313,12 +320,35 @@ public:
 
 private:
     feh_plan &p_;
-    size_t off_[9];
+    size_t off_[9], part_stride_;
     bool solved_, prof_;
 };
 // every load case to the tolerance from u = 0: outputs as feh_solve
 int nodal_solve(feh_plan &p, const double *Ebar_host, double tol, int max_iter, void *strain_dev,
                 double *stress_mean_host, double *energy_host, feh_report *report_host);
+
+// the CG of feh_solve, as the other solvers that run on nodal vectors use it
+int precondition(const feh_plan &p, const void *r, void *z, double *partial, const LcState *st, bool unit_volume,
+                 void *rhat = nullptr);
+int cg_iteration(const feh_plan &p, LcState *st, double tol, int max_iter);
+
+// Stencil derivatives on nodal fields (kern_nodal.hip): the tangent and the
+// residual of the Saint Venant-Kirchhoff law at F = Fbar + B u.  Every launch
+// leaves nodal_num_parts partial sums a row, part_stride apart.
+struct NodalOp {
+    int kind = 0;                  // derivative kind with a nodal stencil
+    const double *u = nullptr;     // [L][D][N]
+    const double *Fbar = nullptr;  // device [L][D][D]
+    double *partial = nullptr;
+};
+bool nodal_kind(int kind, int dim);
+int nodal_num_parts(const feh_plan &p);
+int launch_nodal_tangent(const feh_plan &p, const NodalOp &op, const void *pv, void *q, const LcState *st);  // p.q
+int launch_nodal_residual(const feh_plan &p, const NodalOp &op, void *r);  // |P|^2 over the points
+// rows |B du|^2, then |Fbar + B (u + du)|^2; u += du of the masked load cases
+int launch_nodal_step(const feh_plan &p, const NodalOp &op, double *u, const double *du, const int *mask);
+int launch_nodal_post(const feh_plan &p, const NodalOp &op, void *F, void *P);  // rows: sums of P_ic
+int launch_nodal_reduce(const feh_plan &p, const double *partial, int nq, int nparts, double *out, double scale);
 
 // partial-sum sizes
 int stencil_num_parts(const feh_plan &p);

@@ -24,6 +24,9 @@
 // dE = sym(F^T X), from F and X in registers (FP64 arithmetic).  lambda = mu = 0
 // (vacuum) is allowed.
 //
+// The derivatives with a stencil run the same steps on nodal vectors
+// (fs_solve_nodal), the Fourier derivatives on the fields themselves.
+//
 // Layouts: fields [L][C][N], C = n_e D^2, component (T D + i) D + alpha; the
 // spectrum [L][C][n0][(n1)][nh]; the FFT passes run the L * C scalar fields as
 // one batch.
@@ -395,6 +398,38 @@ FLayout make_flayout(const feh_plan &p, int ne) {
     return Lo;
 }
 
+// The nodal form's vectors in the caller's buffer: the CG's (u the increment),
+// the displacement fluctuation and the Newton mask.
+struct NLayout {
+    NodalWork cg;
+    size_t u, nmask, part_stride, total;
+};
+
+NLayout make_nlayout(const feh_plan &p) {
+    NLayout n{};
+    n.cg = nodal_layout(p);
+    n.part_stride = std::max(p.part_stride, (size_t)nodal_num_parts(p));
+    size_t o = n.cg.total;
+    auto take = [&](size_t b) {
+        const size_t at = o;
+        o = (o + b + 255) & ~size_t(255);
+        return at;
+    };
+    n.u = take((size_t)p.L * p.dim * p.N * sizeof(double));
+    n.nmask = take((size_t)p.L * sizeof(int));
+    n.cg.part = take((size_t)p.L * p.dim * p.dim * n.part_stride * sizeof(double));
+    n.cg.sums = take((size_t)p.L * 9 * sizeof(double));
+    n.total = o;
+    return n;
+}
+
+// Bytes asked of the caller: the deformation-gradient fields, in which the
+// nodal form has room (a plan too small for that asks for what it needs).
+size_t fs_work_bytes(const feh_plan &p, int kind, int ne) {
+    const size_t b = make_flayout(p, ne).total;
+    return nodal_kind(kind, p.dim) ? std::max(b, make_nlayout(p).total) : b;
+}
+
 struct FRun {
     feh_plan &p;
     feh_plan fp;  // the plan seen by the FFT kernels: L * C scalar fields
@@ -412,13 +447,9 @@ int fs_launch_project(const feh_plan &p, const FSK<T> &a, const SymArgs &sa) {
 template <typename T, int DIM>
 int fs_project_dispatch(const feh_plan &p, int kind, const FSK<T> &a, const SymArgs &sa) {
     switch (kind) {
-    case K_FE: return fs_launch_project<T, DIM, K_FE>(p, a, sa);
-    case K_FD: return fs_launch_project<T, DIM, K_FD>(p, a, sa);
-    case K_CD: return fs_launch_project<T, DIM, K_CD>(p, a, sa);
     case K_FOURIER: return fs_launch_project<T, DIM, K_FOURIER>(p, a, sa);
     default:
         if constexpr (DIM == 2) {
-            if (kind == K_LS) return fs_launch_project<T, 2, K_LS>(p, a, sa);
             if (kind == K_FOURIER2) return fs_launch_project<T, 2, K_FOURIER2>(p, a, sa);
         }
         return set_error(FEH_ENOTSUP, "derivative kind not defined in this dimension");
@@ -600,6 +631,119 @@ int fs_solve_t(FRun &R, const double *Fbar_host, const FsParams &prm, void *Fout
     return hip_check(hipStreamSynchronize(p.stream), "finite strain");
 }
 
+// The same Newton steps on nodal vectors, for the derivatives with a stencil.
+// A compatible fluctuation is B u, and with M = B^T B (a scalar per
+// wavevector) G = B M^+ B^T, so CG on B^T K(F) B du = -B^T P preconditioned by
+// M has the steps and the stop of CG on dF = B du: r.z is ||r||^2 of the
+// projected residual, p.q the same product, and r.z of the residual force is
+// ||G P||^2.  Only B^T P is projected, so no part of the right-hand side lies
+// outside the compatible fields and one projection does.  u and du are kept
+// in double: F is formed from u at every use, and an FP32 plan's F carries no
+// rounding of its own.
+int fs_solve_nodal(feh_plan &p, int kind, char *work, const NLayout &Lo, const double *Fbar_host, const FsParams &prm,
+                   void *Fout, void *Pout, FsOut &out) {
+    const int L = p.L, D = p.dim, DD = D * D;
+    NodalScope scope(p, work, Lo.cg);
+    p.part_stride = Lo.part_stride;
+    p.metric = 1 + kind;
+    double *u = reinterpret_cast<double *>(work + Lo.u);
+    int *nmask = reinterpret_cast<int *>(work + Lo.nmask);
+    double *du = p.ptr<double>(p.off_u), *part = p.ptr<double>(p.off_part), *sums = p.ptr<double>(p.off_sums);
+    double *fbar = p.ptr<double>(p.off_ebar);
+    LcState *st = p.ptr<LcState>(p.off_state);
+    NodalOp op;
+    op.kind = kind;
+    op.u = u;
+    op.Fbar = fbar;
+    op.partial = part;
+    p.op = &op;
+    const size_t nvec = (size_t)L * D * p.N;
+    const int np = nodal_num_parts(p);
+    const double w = kind == K_FE ? (D == 3 ? 1.0 / 6.0 : 0.5) : 1.0;
+    auto zero = [&](double *x) { return launch_fill(p, x, nvec * sizeof(double) / p.rsize, 0.0); };  // zero bits
+    auto read = [&](std::vector<double> &h, int n) -> int {
+        h.resize(n);
+        CK(hip_check(hipMemcpyAsync(h.data(), sums, n * sizeof(double), hipMemcpyDeviceToHost, p.stream), "sums"));
+        return hip_check(hipStreamSynchronize(p.stream), "finite strain");
+    };
+    out.newton.assign(L, 0);
+    out.cg.assign(L, 0);
+    out.status.assign(L, FEH_OK);
+    out.rel_eq.assign(L, 0.0);
+    out.rel_inc.assign(L, 0.0);
+    std::vector<double> fb(L * DD), h;
+    std::vector<int> done(L), hmask(L);
+    std::vector<LcState> hs(L);
+    const bool rs = cg_residual_spectral(p);
+    CK(zero(u));
+    for (int s = 1; s <= prm.n_steps; ++s) {
+        for (int k = 0; k < L * DD; ++k) {
+            const double I = (k % DD) / D == (k % DD) % D ? 1.0 : 0.0;
+            fb[k] = I + (double)s / prm.n_steps * (Fbar_host[k] - I);
+        }
+        CK(hip_check(hipMemcpyAsync(fbar, fb.data(), fb.size() * sizeof(double), hipMemcpyHostToDevice, p.stream), "upload Fbar"));
+        std::fill(done.begin(), done.end(), 0);
+        for (int it = 0; it < prm.max_newton; ++it) {
+            // r = -B^T P(F), z = M^+ r; ||P||^2 and r.z = w ||G P||^2
+            void *r = p.ws + (rs ? p.off_q : p.off_r);
+            CK(launch_nodal_residual(p, op, r));
+            CK(launch_nodal_reduce(p, part, L, np, sums, 1.0));
+            CK(precondition(p, r, p.ws + p.off_p, part, nullptr, true, rs ? p.ws + p.off_r : nullptr));
+            CK(launch_nodal_reduce(p, part, L, first_num_parts(p), sums + L, 1.0 / w));
+            CK(read(h, 2 * L));
+            bool any = false;
+            for (int l = 0; l < L; ++l) {
+                if (done[l]) continue;
+                const double nP = std::sqrt(h[l]), nG = std::sqrt(h[L + l]);
+                out.rel_eq[l] = nP > 0.0 ? nG / nP : 0.0;
+                if (nG <= prm.equil_tol * nP) done[l] = 1;
+                any = any || !done[l];
+            }
+            if (!any) break;
+            for (int l = 0; l < L; ++l) {
+                hs[l] = LcState{};
+                hs[l].active = hmask[l] = done[l] ? 0 : 1;
+            }
+            CK(hip_check(hipMemcpyAsync(st, hs.data(), L * sizeof(LcState), hipMemcpyHostToDevice, p.stream), "state"));
+            CK(hip_check(hipMemcpyAsync(nmask, hmask.data(), L * sizeof(int), hipMemcpyHostToDevice, p.stream), "mask"));
+            CK(zero(du));
+            CK(launch_finish_rho(p, st, part, first_num_parts(p), 11, prm.cg_tol, prm.max_cg));
+            int cdone = 0, chunk = 4;
+            while (cdone < prm.max_cg) {
+                CK(hip_check(hipMemcpyAsync(hs.data(), st, L * sizeof(LcState), hipMemcpyDeviceToHost, p.stream),
+                             "read CG state"));
+                CK(hip_check(hipStreamSynchronize(p.stream), "finite strain CG"));
+                bool cg_any = false;
+                for (const LcState &x : hs) cg_any = cg_any || x.active;
+                if (!cg_any) break;
+                const int c = std::min(chunk, prm.max_cg - cdone);
+                for (int k = 0; k < c; ++k) CK(cg_iteration(p, st, prm.cg_tol, prm.max_cg));
+                cdone += c;
+                if (chunk < 16) chunk *= 2;
+            }
+            CK(launch_finalize_u(p, du, p.ws + p.off_p, st));
+            CK(hip_check(hipMemcpyAsync(hs.data(), st, L * sizeof(LcState), hipMemcpyDeviceToHost, p.stream),
+                         "read CG state"));
+            CK(launch_nodal_step(p, op, u, du, nmask));
+            CK(launch_nodal_reduce(p, part, 2 * L, np, sums, 1.0));
+            CK(read(h, 2 * L));
+            for (int l = 0; l < L; ++l) {
+                if (done[l]) continue;
+                out.newton[l] += 1;
+                out.cg[l] += hs[l].iters;
+                const double nd = std::sqrt(h[l]), nf = std::sqrt(h[L + l]);
+                out.rel_inc[l] = nf > 0.0 ? nd / nf : 0.0;
+                if (nd <= prm.newton_tol * nf) done[l] = 1;
+            }
+        }
+        for (int l = 0; l < L; ++l)
+            if (!done[l]) out.status[l] = FEH_ENOCONV;
+    }
+    CK(launch_nodal_post(p, op, Fout, Pout));
+    CK(launch_nodal_reduce(p, part, L * DD, np, sums, 1.0 / ((double)p.N * points_of(kind, D))));
+    return read(out.pmean, L * DD);
+}
+
 }  // namespace
 }  // namespace feh
 
@@ -611,7 +755,7 @@ int feh_finite_strain_workspace_bytes(const feh_plan *plan, int kind, size_t *by
     if (!plan || !bytes) return set_error(FEH_EINVAL, "null argument");
     const int ne = points_of(kind, plan->dim);
     if (ne < 1) return set_error(FEH_ENOTSUP, "derivative kind not defined in this dimension");
-    *bytes = make_flayout(*plan, ne).total;
+    *bytes = fs_work_bytes(*plan, kind, ne);
     return FEH_OK;
 }
 
@@ -650,7 +794,7 @@ int feh_finite_strain_solve(feh_plan *plan, int kind, const double *Fbar_host, i
             if (!(det > 0.0)) return set_error(FEH_EINVAL, "Fbar must have a positive determinant");
         }
         const FLayout Lo = make_flayout(p, ne);
-        if (!work_dev || work_bytes < Lo.total) return set_error(FEH_ENOMEM, "finite-strain workspace missing or too small");
+        if (!work_dev || work_bytes < fs_work_bytes(p, kind, ne)) return set_error(FEH_ENOMEM, "finite-strain workspace missing or too small");
         if (reinterpret_cast<uintptr_t>(work_dev) % 256) return set_error(FEH_EINVAL, "workspace must be 256-byte aligned");
         const int C = ne * D * D;
         FRun R{p, p, kind, ne, C, Lo, static_cast<char *>(work_dev)};
@@ -661,7 +805,9 @@ int feh_finite_strain_solve(feh_plan *plan, int kind, const double *Fbar_host, i
         FsParams prm{n_steps, max_newton, max_cg, newton_tol, equil_tol, cg_tol};
         FsOut out;
         int rc;
-        if (p.prec == FEH_FP64)
+        if (nodal_kind(kind, D))
+            rc = fs_solve_nodal(p, kind, R.w, make_nlayout(p), Fbar_host, prm, F_dev, P_dev, out);
+        else if (p.prec == FEH_FP64)
             rc = D == 3 ? fs_solve_t<double, 3>(R, Fbar_host, prm, F_dev, P_dev, out)
                         : fs_solve_t<double, 2>(R, Fbar_host, prm, F_dev, P_dev, out);
         else

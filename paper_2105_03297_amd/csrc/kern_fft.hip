@@ -394,6 +394,8 @@ struct FK {
     double out_scale, invN, chalf;  // chalf = element volume / 2
     float near0;              // FP32 plans: sum_a |aa_a|^2 below which M^-1 is formed in FP64
     float hmax_f, post_f;     // FP32 plans: h_max and h_max^2 / chalf (scale-free FP32 inverse)
+    int metric;               // feh_plan::metric, and for 1 + kind the point weight and the smallest symbol
+    double metric_w, metric_tiny;
     T *minv;                  // (B^*B)^-1 table [block][component][slot] (first-axis pass)
     int minv_q;               // 0: slots in order; Q: interleaved for Q-wide loads (see minv_pos)
 };
@@ -1352,6 +1354,37 @@ __device__ __forceinline__ void slot_inverse(const FK<T> &a, int e, int PB, long
     for (int c = 0; c < 3; ++c) mo[c] = Cx<T>{T(Io[c].x), T(Io[c].y)};
 }
 
+// 1 / (w sum_Ta |D_Ta|^2) at wavevector slot e for the full gradient of a
+// stencil derivative (metric 1 + kind), from the per-axis factors
+// aa = (e^{i k h} - 1) / h; 0 where the symbol vanishes.
+template <typename T, int DIM>
+__device__ __forceinline__ T slot_scalar_metric(const FK<T> &a, int e, int PB, long long in0, int lim, const Cx<double> *pin) {
+    const int j = (int)a.d_PB.div((uint32_t)e);
+    const int b = e - j * PB;
+    if (!(e < PB * a.n0 && b * DIM < lim && !(j == 0 && in0 + b == 0))) return T(0);
+    Cx<double> A[3], W[3];
+    A[0] = ld2(a.aa[0], j);
+    W[0] = ld2(a.om[0], j);
+    A[1] = pin[4 * b + 0];
+    W[1] = pin[4 * b + 1];
+    if constexpr (DIM == 3) A[2] = pin[4 * b + 2];
+    double S = 0.0;
+    switch (a.metric - 1) {
+    case FEH_DERIV_CD:  // i sin(k h) / h
+        #pragma unroll
+        for (int x = 0; x < DIM; ++x) S += A[x].y * A[x].y;
+        break;
+    case FEH_DERIV_LS:  // (w_a - 1)(1 + w_b) / (2 h_a): |1 + w|^2 / 4 = (1 + Re w) / 2
+        S = 0.5 * (nrm(A[0]) * (1.0 + W[1].x) + nrm(A[1]) * (1.0 + W[0].x));
+        break;
+    default:  // forward differences; linear elements take the same edge differences once an element
+        #pragma unroll
+        for (int x = 0; x < DIM; ++x) S += nrm(A[x]);
+        if (a.metric - 1 == FEH_DERIV_FE) S *= DIM == 3 ? 6.0 : 2.0;
+    }
+    return S > a.metric_tiny ? T(1.0 / (a.metric_w * S)) : T(0);
+}
+
 // z = M^-1 r at one wavevector (md: real diagonal, mo: upper triangle of
 // M^-1) and the Parseval term Re(r . conj z) in FP64.
 template <typename T, int DIM>
@@ -1424,7 +1457,14 @@ __global__ __launch_bounds__(kFftThreads) void k_first_table(FK<T> a) {
         T md[D];
         Cx<T> mo[3];
         bool half;
-        slot_inverse<T, DIM>(a, e, PB, in0, lim, pin, md, mo, half);
+        if (a.metric == 0) {
+            slot_inverse<T, DIM>(a, e, PB, in0, lim, pin, md, mo, half);
+        } else {
+            const T m = slot_scalar_metric<T, DIM>(a, e, PB, in0, lim, pin);
+            #pragma unroll
+            for (int c = 0; c < D; ++c) md[c] = m;
+            mo[0] = mo[1] = mo[2] = Cx<T>{T(0), T(0)};
+        }
         const int pos = minv_pos(e, a.minv_q);
         #pragma unroll
         for (int c = 0; c < D; ++c) tb[c * cntk + pos] = md[c];
@@ -1802,6 +1842,9 @@ FK<T> base_args(const feh_plan &p, const FftArgs &fa) {
     a.near0 = (float)(0.0625 / (hmax * hmax));  // |k| h_max < 1/4
     a.hmax_f = (float)hmax;
     a.post_f = (float)(hmax * hmax / a.chalf);
+    a.metric = p.metric;
+    a.metric_w = p.metric == 1 + FEH_DERIV_FE ? (p.dim == 3 ? 1.0 / 6.0 : 0.5) : 1.0;
+    for (int ax = 0; ax < p.dim; ++ax) a.metric_tiny += 1e-24 / (p.h[ax] * p.h[ax]);
     a.tw_last = p.ptr<const Cx<T>>(p.off_tw[p.dim - 1]);
     for (int ax = 0; ax < 3; ++ax) {
         a.om[ax] = p.ptr<const double>(p.off_om[ax]);
@@ -2050,7 +2093,8 @@ int first_t(const feh_plan &p, const FftArgs &fa, int mode) {
     a.d_PB = FastDiv::make((uint32_t)PB);
     a.nbd = FastDiv::make((uint32_t)(PB * DIM));
     a.nblk = (int)((a.inner_total + PB - 1) / PB);
-    const bool perlc = first_per_load_case(p);
+    // the metrics other than M are only in the table, which this layout reads
+    const bool perlc = first_per_load_case(p) || p.metric != 0;
     a.total = perlc ? a.nblk * p.L : a.nblk;  // one block per (load case, pencils) or per pencils
     dim3 g(a.total), b(kFftThreads);
     const bool gen = !pow2_len(a.ax.n);
@@ -2065,13 +2109,14 @@ int first_t(const feh_plan &p, const FftArgs &fa, int mode) {
         a.minv = p.ptr<T>(p.off_minv);
         // the compile-time pass reads the table with lane-interleaved slots
         a.minv_q = ctpb > 0 ? 16 / (int)sizeof(T) : 0;
-        if (p.minv_ws != p.ws || p.minv_pb != PB || p.minv_q != a.minv_q) {
+        if (p.minv_ws != p.ws || p.minv_pb != PB || p.minv_q != a.minv_q || p.minv_metric != p.metric) {
             hipLaunchKernelGGL((k_first_table<T, DIM>), dim3(a.nblk), b, 0, p.stream, a);
             const int rc = hip_check(hipGetLastError(), "inverse table launch");
             if (rc != FEH_OK) return rc;
             p.minv_ws = p.ws;
             p.minv_pb = PB;
             p.minv_q = a.minv_q;
+            p.minv_metric = p.metric;
         }
     }
     if (ctpb > 0) {

@@ -70,3 +70,57 @@ def test_plan_solution_survives_fe_strain_cg(prec):
     assert torch.equal(ga[0], gb[0]) and torch.equal(ga[1], gb[1])
     assert torch.equal(a["u"], b["u"]) and np.array_equal(a["energy"], b["energy"])
     hz.close()
+
+
+FINITE = [("fe", (6, 128), "fp32"), ("fe", (64, 6), "fp64"), ("fe", (64, 6), "fp32"), ("fe", (4, 9, 3), "fp64"),
+          ("fd", (64, 5), "fp64"), ("cd", (5, 128), "fp32"), ("cd", (6, 4), "fp64"), ("ls", (8, 6), "fp64"),
+          ("ls", (64, 4), "fp32"), ("fd", (3, 4, 5), "fp32"), ("cd", (4, 3, 5), "fp64")]
+
+
+@pytest.mark.parametrize("kind,shape,prec", FINITE)
+def test_finite_strain_on_nodal_vectors(kind, shape, prec):
+    """F against the oracle's Newton solution with compile-time and run-time
+    passes and every stencil (even grids: central differences and least
+    squares have modes without a gradient).  Newton is quadratic, so the last
+    step, of at most the tolerance, leaves its square: what remains is the CG
+    tolerance of that step and the rounding of the CG vectors, both relative
+    to it, and FP32's rounding of F itself (6e-8)."""
+    from oracle import finite
+    from paper_2105_03297_amd import Homogenizer
+    dim = len(shape)
+    say("finite nodal", kind, shape, prec)
+    lam, mu = random_material(shape, seed=19, prec=prec, emax=4.0)
+    rng = np.random.default_rng(6)
+    Fbar = np.array([np.eye(dim) * 1.03 + 0.02 * rng.standard_normal((dim, dim)) for _ in range(2)])
+    tol = 1e-9 if prec == "fp64" else 1e-4
+    hz = Homogenizer(shape, n_load=2, precision=prec)
+    hz.set_material(lam=lam, mu=mu)
+    out = hz.finite_strain_solve(Fbar, kind=kind, newton_tol=tol, equil_tol=0.0, cg_tol=1e-3 * tol if prec == "fp64" else tol,
+                                 fields=True)
+    got = out["F"].cpu().numpy().astype(np.float64)
+    hz.close()
+    for l in range(2):
+        assert out["report"][l]["status"] == 0
+        ref, _, _ = finite.solve(lam, mu, Fbar[l], kind, newton_tol=1e-12, equil_tol=1e-12, cg_tol=1e-10)
+        ref = ref.reshape(got[l].shape)
+        assert np.abs(got[l] - ref).max() <= (1e-10 if prec == "fp64" else 1e-6)
+
+
+def test_plan_solution_survives_finite_strain():
+    """The inverse table of the plan is rebuilt for each metric: a small-strain
+    solve after a finite-strain one repeats the first bitwise."""
+    import torch
+    from paper_2105_03297_amd import Homogenizer
+    say("tables")
+    for shape in ((64, 6), (9, 7, 5)):
+        dim = len(shape)
+        lam, mu = random_material(shape, seed=3)
+        Eb = _ebars(dim, 2)
+        hz = Homogenizer(shape, n_load=2)
+        hz.set_material(lam=lam, mu=mu)
+        a = hz.solve(Eb, tol=1e-8, return_u=True)
+        for kind in ("fe", "fd"):
+            hz.finite_strain_solve(np.stack([np.eye(dim) * 1.02] * 2), kind=kind, max_newton=3)
+            b = hz.solve(Eb, tol=1e-8, return_u=True)
+            assert torch.equal(a["u"], b["u"]) and np.array_equal(a["energy"], b["energy"])
+        hz.close()
