@@ -231,7 +231,8 @@ int feh_plan_autotune(feh_plan *plan, int reps);
  * pencils per workgroup (axis 1), pencils per workgroup (axis 0) (0 =
  * default heuristic), axis-0 workgroup layout (1: one workgroup per load
  * case, the default for a power-of-two axis 0; 0: every load case in one
- * workgroup, the default otherwise), stencil tile rows (3D: 8 or
+ * workgroup, the default otherwise; a plan whose schedule was never set or
+ * tuned takes 1 for the CG's pass at every length), stencil tile rows (3D: 8 or
  * 16 rows of 32 voxels; 2D: 1)], then for each axis 0..2 the
  * number of passes followed by the radices in pass order, then 1 if passes
  * whose shape has a compile-time transform may use it (power-of-two axes of

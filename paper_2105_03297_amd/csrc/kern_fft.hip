@@ -2093,8 +2093,15 @@ int first_t(const feh_plan &p, const FftArgs &fa, int mode) {
     a.d_PB = FastDiv::make((uint32_t)PB);
     a.nbd = FastDiv::make((uint32_t)(PB * DIM));
     a.nblk = (int)((a.inner_total + PB - 1) / PB);
-    // the metrics other than M are only in the table, which this layout reads
-    const bool perlc = first_per_load_case(p) || p.metric != 0;
+    // The CG's pass, unless the layout was set: one workgroup per load case at
+    // every length.  It reads the inverses from the table (the only place of
+    // the metrics other than M), so it has n_load times the workgroups of the
+    // cached variant at no arithmetic more, and was at least as fast at every
+    // size (a solve, FP32 3D: 90x77x105 12.6 -> 11.1 ms, 45x50x39 5.7 -> 3.8,
+    // 160^3 44.0 -> 37.0; FP64 2D: 151^2 25.1 -> 13.4, 300^2 5.2 -> 3.7,
+    // 900^2 9.9 -> 10.0).
+    const bool table = mode == 0 && fa.unit_volume;
+    const bool perlc = first_per_load_case(p) || p.metric != 0 || (table && p.tune_first_perlc == 0);
     a.total = perlc ? a.nblk * p.L : a.nblk;  // one block per (load case, pencils) or per pencils
     dim3 g(a.total), b(kFftThreads);
     const bool gen = !pow2_len(a.ax.n);
@@ -2104,7 +2111,7 @@ int first_t(const feh_plan &p, const FftArgs &fa, int mode) {
     // the CG's fused pass (element volume relative to the voxel) reads the
     // (B^*B)^-1 table, built here on the first use for this workspace and
     // block size; the test exports (true volume) form the inverses in place
-    const bool tab = mode == 0 && perlc && fa.unit_volume;
+    const bool tab = table && perlc;
     if (tab) {
         a.minv = p.ptr<T>(p.off_minv);
         // the compile-time pass reads the table with lane-interleaved slots
