@@ -16,6 +16,7 @@
 //   y[q + m (p + L* d)] = sum_c exp(-2 pi i c d / R) w_n^{c p m} x[q + c m + m R p]
 // for q < m, p < L*, d < R.
 #include <algorithm>
+#include <type_traits>
 
 #include "device_common.hpp"
 
@@ -47,8 +48,8 @@ extern __shared__ double feh_dyn_lds[];
 // FP64 transforms of general lengths (radix 3..13 and direct passes) are held
 // to at most 256 VGPRs, two waves per SIMD; with tiles sized to the pass, two
 // workgroups then fit a CU for rows of up to about 1700 points.
-template <typename T, bool GEN>
-constexpr int kGenWaves = (GEN && sizeof(T) == 8) ? 2 : 1;
+template <typename T, int GEN>
+constexpr int kGenWaves = (GEN != 0 && sizeof(T) == 8) ? 2 : 1;
 
 // LDS one workgroup may hold on gfx950 (160 KiB).  Every launch checks its
 // static plus dynamic LDS against it on the host and reports FEH_ENOTSUP
@@ -253,7 +254,8 @@ __device__ __forceinline__ void stockham_pass(Cx<T> *buf, int nb, const FastDiv 
     __syncthreads();
 }
 
-// Pass with a prime radix R > 13 (known at run time only), each butterfly's
+// Pass with a prime radix R > 13 (known at run time only) whose tile is too
+// narrow for prime_pass (few butterflies of a large prime), each butterfly's
 // outputs evaluated directly:
 //   y[q + m (p + L* d)] = sum_c w_n^{c m (p + L* d)} x[q + c m + m R p].
 // A thread takes B consecutive outputs d0 .. d0 + B - 1 of one butterfly and
@@ -331,9 +333,145 @@ __device__ __forceinline__ void direct_pass(Cx<T> *buf, int nb, int n, const Pas
     __syncthreads();
 }
 
-// GEN = false instantiates only the radices of power-of-two lengths (2, 4, 8),
-// which keeps the register footprint of the common case small.
-template <typename T, int PPT, bool GEN>
+// Matrix-core tile D = A B + C of 16 rows, 16 columns and 4 inner steps (one
+// wavefront): lane l holds A(l % 16, l / 16) and B(l / 16, l % 16).
+template <typename T>
+struct Mfma;
+template <>
+struct Mfma<double> {
+    typedef double Acc __attribute__((ext_vector_type(4)));
+    static __device__ __forceinline__ Acc run(double a, double b, Acc c) {
+        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+    }
+    static __device__ __forceinline__ int row(int lane, int r) { return 4 * r + (lane >> 4); }  // of c[r]
+};
+template <>
+struct Mfma<float> {
+    typedef float Acc __attribute__((ext_vector_type(4)));
+    static __device__ __forceinline__ Acc run(float a, float b, Acc c) {
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+    }
+    static __device__ __forceinline__ int row(int lane, int r) { return 4 * (lane >> 4) + r; }
+};
+
+// Tiles of prime_pass a wavefront may hold: what the accumulators of a
+// workgroup's PPT points a thread need, with room for rounding up.
+template <int PPT>
+constexpr int kPrimeTiles = PPT <= 6 ? 4 : PPT <= 16 ? 8 : 12;
+__host__ __device__ inline int prime_tiles(int points, int R) {
+    const int rows = ((R - 1) / 2 + 1 + 15) / 16, cols = (2 * (points / R) + 15) / 16;
+    return (rows * cols + kFftThreads / 64 - 1) / (kFftThreads / 64);
+}
+
+// Pass with a prime radix R > 13 (known at run time only) as a product with
+// the matrix cores.  With s_c = x_c + x_{R-c}, d_c = x_c - x_{R-c} (c = 1 ..
+// H = (R - 1) / 2, inputs times their Stockham twiddles) the outputs are
+//   A_k = x_0 + sum_c s_c cos(2 pi c k / R), B_k = sum_c d_c sin(2 pi c k / R),
+//   y_k = A_k -+ i B_k, y_{R-k} = A_k +- i B_k      (k = 0 .. H),
+// a quarter of the multiplications of the sum over all c, and two real
+// products of a table with the real and imaginary parts of every butterfly
+// as columns.  The direct sum (direct_pass, below) spends an LDS read of a
+// twiddle for every few multiplications; here a lane reads one table entry
+// and two operands for 16 x 16 x 4 x 2 of them.  Measured, FP64 (with the small
+// tiles for the first): 151^2 Fourier strain-space solve 22.6 -> 3.3 ms; 1661^2
+// FE solve 48.9 -> 19.7 ms.
+template <typename T, int PPT>
+__device__ __forceinline__ void prime_pass(Cx<T> *buf, int nb, const FastDiv &nbd, int n, const PassInfo &ps,
+                                           const Cx<T> *tw, int tws, bool inv, int tx) {
+    constexpr int NT = kFftThreads, NW = NT / 64, MT = kPrimeTiles<PPT>;
+    using M = Mfma<T>;
+    const int R = ps.R, m = (int)ps.m.d, Ls = ps.Lstar, H = (R - 1) / 2;
+    const int nR = n / R, bf = nb * nR;         // butterflies
+    auto input = [&](int w) {                   // element 0 of butterfly w
+        const int r = (int)nbd.div((uint32_t)w), b = w - r * nb;
+        const int p = (int)ps.m.div((uint32_t)r), q = r - p * m;
+        return (q + m * R * p) * nb + b;
+    };
+    const int cs = m * nb;                      // between inputs
+    // ---- s_c in the place of x_c, d_c in that of x_{R-c}
+    for (int i = tx; i < bf * H; i += NT) {
+        const int c = 1 + i / bf, w = i - (c - 1) * bf;
+        const int r = (int)nbd.div((uint32_t)w);
+        const int pm = (int)ps.m.div((uint32_t)r) * m;
+        Cx<T> *x0 = buf + input(w);
+        Cx<T> x = x0[c * cs], y = x0[(R - c) * cs];
+        if (pm != 0) {
+            x = cmul(x, twid(tw, tws, c * pm, inv));
+            y = cmul(y, twid(tw, tws, (R - c) * pm, inv));
+        }
+        x0[c * cs] = cadd(x, y);
+        x0[(R - c) * cs] = csub(x, y);
+    }
+    __syncthreads();
+    // ---- tiles of 16 outputs k by 16 columns (8 butterflies, real and imaginary)
+    const int lane = tx & 63, wv = tx >> 6, li = lane & 15, lg = lane >> 4;
+    const int KT = (H + 1 + 15) / 16, CT = (2 * bf + 15) / 16;
+    typename M::Acc A[MT], B[MT];
+    const T *re = reinterpret_cast<const T *>(buf);
+    #pragma unroll
+    for (int i = 0; i < MT; ++i) {
+        const int t = wv + NW * i;
+        if (t < KT * CT) {                      // the same for the whole wavefront
+            const int ct = t / KT, kt = t - ct * KT;
+            const int col = ct * 16 + li, w = col >> 1;
+            const bool on = w < bf;
+            const T *x0 = re + 2 * input(on ? w : 0) + (col & 1);
+            const int k = min(kt * 16 + li, H);
+            const T first = on ? x0[0] : T(0);
+            typename M::Acc a = {first, first, first, first}, b = {T(0), T(0), T(0), T(0)};
+            int c = 1 + lg;
+            int e = (c * k) % R;
+            const int step = (4 * k) % R;
+            for (int c0 = 1; c0 <= H; c0 += 4) {
+                const Cx<T> wt = tw[e * nR * tws];  // cos, -sin
+                const bool in = on && c <= H;
+                const int cc = in ? c : 1;
+                const T sv = x0[2 * cc * cs], dv = x0[2 * (R - cc) * cs];
+                a = M::run(wt.x, in ? sv : T(0), a);
+                b = M::run(-wt.y, in ? dv : T(0), b);
+                c += 4;
+                e += step;
+                if (e >= R) e -= R;
+            }
+            A[i] = a;
+            B[i] = b;
+        }
+    }
+    __syncthreads();
+    T *out = reinterpret_cast<T *>(buf);
+    const int os = m * Ls * nb;                 // between outputs
+    #pragma unroll
+    for (int i = 0; i < MT; ++i) {
+        const int t = wv + NW * i;
+        if (t < KT * CT) {
+            const int ct = t / KT, kt = t - ct * KT;
+            const int col = ct * 16 + li, w = col >> 1;
+            const int r1 = (int)nbd.div((uint32_t)w), b1 = w - r1 * nb;
+            const int p = (int)ps.m.div((uint32_t)r1), q = r1 - p * m;
+            T *y0 = out + 2 * ((q + m * p) * nb + b1) + (col & 1);
+            #pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int k = kt * 16 + M::row(lane, r);
+                // -i B = (B_im, -B_re), the other part being the neighbouring
+                // column's; + i B for the inverse
+                const T bx = __shfl_xor(B[i][r], 1);
+                const T ib = ((col & 1) != 0) == inv ? bx : -bx;
+                if (w < bf && k <= H) {
+                    y0[2 * k * os] = A[i][r] + ib;
+                    if (k > 0) y0[2 * (R - k) * os] = A[i][r] - ib;
+                }
+            }
+        }
+    }
+    __syncthreads();
+}
+
+// Passes that an instantiation holds, so that a length does not pay the
+// registers of passes it has none of: GEN = 0 the radices of power-of-two
+// lengths (2, 4, 8), 1 also 3 to 13, 2 also the prime passes (the matrix-core
+// accumulators of prime_pass in the kernels of lengths without a prime above
+// 13 took a solve on 90 x 77 x 105 in FP32 from 11.1 to 16.1 ms).
+template <typename T, int PPT, int GEN>
 __device__ __forceinline__ void lds_fft(Cx<T> *buf, int nb, const FastDiv &nbd, const AxisFFT &ax,
                                         const Cx<T> *tw, int tws, bool inv, int tx = threadIdx.x) {
     for (int s = 0; s < ax.npass; ++s) {
@@ -343,14 +481,20 @@ __device__ __forceinline__ void lds_fft(Cx<T> *buf, int nb, const FastDiv &nbd, 
         case 4: stockham_pass<T, 4, PPT>(buf, nb, nbd, ax.n, ps, tw, tws, inv, tx); break;
         case 8: stockham_pass<T, 8, PPT>(buf, nb, nbd, ax.n, ps, tw, tws, inv, tx); break;
         default:
-            if constexpr (GEN) {
+            if constexpr (GEN != 0) {
                 switch (ps.R) {
                 case 3: stockham_pass<T, 3, PPT>(buf, nb, nbd, ax.n, ps, tw, tws, inv, tx); break;
                 case 5: stockham_pass<T, 5, PPT>(buf, nb, nbd, ax.n, ps, tw, tws, inv, tx); break;
                 case 7: stockham_pass<T, 7, PPT>(buf, nb, nbd, ax.n, ps, tw, tws, inv, tx); break;
                 case 11: stockham_pass<T, 11, PPT>(buf, nb, nbd, ax.n, ps, tw, tws, inv, tx); break;
                 case 13: stockham_pass<T, 13, PPT>(buf, nb, nbd, ax.n, ps, tw, tws, inv, tx); break;
-                default: direct_pass<T, PPT>(buf, nb, ax.n, ps, tw, tws, inv, tx); break;
+                default:
+                    if constexpr (GEN == 2) {
+                        if (prime_tiles(nb * ax.n, ps.R) <= kPrimeTiles<PPT>)
+                            prime_pass<T, PPT>(buf, nb, nbd, ax.n, ps, tw, tws, inv, tx);
+                        else direct_pass<T, PPT>(buf, nb, ax.n, ps, tw, tws, inv, tx);
+                    }
+                    break;
                 }
             }
             break;
@@ -566,7 +710,7 @@ constexpr int ct_batches() { return (sizeof(T) == 4 ? 16 : 8) * kFftThreads / N;
 // into the block so the loads stay in bounds; their values are discarded),
 // then every store; r and r_out may be the same buffer.
 // ---------------------------------------------------------------------------
-template <typename T, int PPT, bool GEN, bool AXPY>
+template <typename T, int PPT, int GEN, bool AXPY>
 __global__ __launch_bounds__(kFftThreads) __attribute__((amdgpu_waves_per_eu(kGenWaves<T, GEN>))) void k_last_fwd(FK<T> a) {
     constexpr int NT = kFftThreads;
     __shared__ Cx<T> sbuf[GEN ? 1 : PPT * NT];
@@ -591,7 +735,7 @@ __global__ __launch_bounds__(kFftThreads) __attribute__((amdgpu_waves_per_eu(kGe
     stage(twl, a.tw_last, a.nlast);
     const long long lbase = (long long)lc * D * N + s0 * a.nlast;
     // AXPY keeps two loads per slot in flight: 8 slots per round
-    constexpr int CH = AXPY ? 8 : PPT;
+    constexpr int CH = AXPY && PPT > 8 ? 8 : PPT;
     #pragma unroll
     for (int h = 0; h < PPT; h += CH) {
         Cx<T> v[CH];
@@ -680,7 +824,7 @@ __global__ __launch_bounds__(kFftThreads) __attribute__((amdgpu_waves_per_eu(kGe
 // type u is kept in (T, or double in an FP32 plan whose caller differentiates
 // u and must not lose the digits that its rounding to float would take).
 // ---------------------------------------------------------------------------
-template <typename T, int PPT, bool GEN, bool UPD, typename U = T>
+template <typename T, int PPT, int GEN, bool UPD, typename U = T>
 __global__ __launch_bounds__(kFftThreads) __attribute__((amdgpu_waves_per_eu(kGenWaves<T, GEN>))) void k_last_inv(FK<T> a) {
     constexpr int NT = kFftThreads;
     __shared__ Cx<T> sbuf[GEN ? 1 : PPT * NT];
@@ -769,7 +913,7 @@ __global__ __launch_bounds__(kFftThreads) __attribute__((amdgpu_waves_per_eu(kGe
         const T beta = T(a.st[lc].beta);
         const U ap = U(a.st[lc].alpha_pend);
         U *uu = static_cast<U *>(a.u_upd);
-        constexpr int CH = 8;  // slots per round: two loads each in flight
+        constexpr int CH = PPT > 8 ? 8 : PPT;  // slots per round: two loads each in flight
         #pragma unroll
         for (int h = 0; h < PPT; h += CH) {
             Cx<T> pv[CH];
@@ -1108,7 +1252,7 @@ __global__ __launch_bounds__(kFftThreads) void k_last_inv_ct(FK<T> a) {
 // ---------------------------------------------------------------------------
 // middle axis (3D), complex to complex
 // ---------------------------------------------------------------------------
-template <typename T, int PPT, bool GEN>
+template <typename T, int PPT, int GEN>
 __global__ __launch_bounds__(kFftThreads) __attribute__((amdgpu_waves_per_eu(kGenWaves<T, GEN>))) void k_middle(FK<T> a, int inv) {
     constexpr int NT = kFftThreads;
     __shared__ Cx<T> sbuf[GEN ? 1 : PPT * NT];
@@ -1486,7 +1630,7 @@ __global__ __launch_bounds__(kFftThreads) void k_first_table(FK<T> a) {
 // side on one XCD); the inverses are read from the table of k_first_table
 // (TAB) or formed again per load case just in time.  The power-of-two PERLC
 // instantiations are held to 3 waves per SIMD (at most 168 VGPRs, no spills).
-template <typename T, int PPT, int DIM, int MODE, bool GEN, bool PERLC, bool TAB>
+template <typename T, int PPT, int DIM, int MODE, int GEN, bool PERLC, bool TAB>
 __global__ __launch_bounds__(kFftThreads) __attribute__((amdgpu_waves_per_eu((PERLC && !GEN) ? 3 : 1))) void k_first(FK<T> a) {
     constexpr int NT = kFftThreads;
     constexpr int D = DIM;
@@ -1807,6 +1951,16 @@ __global__ __launch_bounds__(kFftThreads) void k_first_ct(FK<T> a) {
 // ---------------------------------------------------------------------------
 bool pow2_len(int n) { return n > 0 && (n & (n - 1)) == 0; }
 
+// Calls f with the GEN of an axis' passes.
+template <typename F>
+void with_gen(const AxisFFT &ax, F f) {
+    bool prime = false;
+    for (int s = 0; s < ax.npass; ++s) prime = prime || ax.pass[s].R > 13;
+    if (pow2_len(ax.n)) f(std::integral_constant<int, 0>{});
+    else if (!prime) f(std::integral_constant<int, 1>{});
+    else f(std::integral_constant<int, 2>{});
+}
+
 template <typename T>
 FK<T> base_args(const feh_plan &p, const FftArgs &fa) {
     FK<T> a{};
@@ -1856,8 +2010,29 @@ FK<T> base_args(const feh_plan &p, const FftArgs &fa) {
     return a;
 }
 
-template <typename T>
-constexpr int ppt() { return sizeof(T) == 4 ? 24 : 16; }
+// Points a thread of a run-time pass holds: the tile of a workgroup is up to
+// kFftThreads times as many, SMALL a quarter of it.
+template <typename T, bool SMALL = false>
+constexpr int ppt() { return (sizeof(T) == 4 ? 24 : 16) / (SMALL ? 4 : 1); }
+
+// Workgroups that fill the chip: four on each of its 256 CUs.  A run-time
+// pass with fewer (small grids, few load cases) takes the small tile: a launch
+// then lasts as long as one workgroup, whose instructions are issued for every
+// slot a thread may hold, used or not, and the small tile has a quarter of
+// them and spreads the rows over more CUs.
+// Measured, a solve: FP64 32^2 x 3 load cases 2.15 -> 1.68 ms, FP32 64^3 x 6 (its
+// last axis only) 25.2 -> 22.6, FP64 1024^2 unchanged (it fills the chip).
+constexpr long long kFillWorkgroups = 1024;
+// rows or pencils of a pass's workgroup: `most` at the full tile; the small
+// tile's `small` (0: the axis does not fit it) where the full one leaves the
+// chip part empty, thinned out further while that gives every CU a workgroup
+inline bool small_tile(long long units, int most, int small, long long per_unit, int *take) {
+    *take = most;
+    if (small < 1 || (units + most - 1) / most * per_unit >= kFillWorkgroups) return false;
+    const long long thin = (units * per_unit + 255) / 256;
+    *take = (int)std::max<long long>(1, std::min<long long>(small, thin));
+    return true;
+}
 
 // LDS of a last- or middle-axis pass whose tile holds `cnt` points, in
 // bytes (static tile plus dynamic part).  Power-of-two lengths keep a static
@@ -1868,8 +2043,7 @@ constexpr int ppt() { return sizeof(T) == 4 ? 24 : 16; }
 // leave room for a second resident workgroup.  *lbuf receives the dynamic
 // tile's entries (0 for power-of-two lengths), *dyn the dynamic bytes.
 template <typename T>
-size_t lds_of_pass(bool gen, int cnt, int table, int *lbuf, size_t *dyn) {
-    constexpr int PPT = sizeof(T) == 4 ? 24 : 16;
+size_t lds_of_pass(bool gen, int cnt, int table, int *lbuf, size_t *dyn, int PPT) {
     constexpr int q = 16 / (int)sizeof(Cx<T>);
     *lbuf = gen ? (cnt + q - 1) / q * q : 0;
     *dyn = ((size_t)*lbuf + table) * sizeof(Cx<T>);
@@ -1907,6 +2081,7 @@ int last_t(const feh_plan &p, const FftArgs &fa, bool inverse) {
     if (RR > 64) RR = 64;
     if (p.tune_rr_last > 0 && p.tune_rr_last < RR) RR = p.tune_rr_last;
     if (RR > a.rows) RR = (int)a.rows;
+    const bool small = p.tune_rr_last == 0 && small_tile(a.rows, RR, std::min(RR, ppt<T, true>() * kFftThreads / (nc * a.D)), p.L, &RR);
     a.RR = RR;
     a.nbd = FastDiv::make((uint32_t)(a.D * RR));
     a.d_nc = FastDiv::make((uint32_t)nc);
@@ -1955,33 +2130,45 @@ int last_t(const feh_plan &p, const FftArgs &fa, bool inverse) {
     }
     const dim3 g(a.total), b(kFftThreads);
     const bool gen = !pow2_len(a.ax.n);
-    size_t dyn;
-    if (lds_of_pass<T>(gen, a.D * RR * nc, a.nlast, &a.lbuf, &dyn) > kLdsPerWorkgroup)
-        return set_error(FEH_ENOTSUP, "last axis too long for the LDS transform");
-    if (inverse) {
-        const bool upd = fa.p_upd != nullptr;
-        if (upd && (fa.u_upd == nullptr || fa.state == nullptr))
-            return set_error(FEH_EINVAL, "fused CG update needs p, u and the CG state");
-        if (upd && fa.u_f64) {
-            if (gen) hipLaunchKernelGGL((k_last_inv<T, PPT, true, true, double>), g, b, dyn, p.stream, a);
-            else hipLaunchKernelGGL((k_last_inv<T, PPT, false, true, double>), g, b, dyn, p.stream, a);
-        } else if (upd) {
-            if (gen) hipLaunchKernelGGL((k_last_inv<T, PPT, true, true>), g, b, dyn, p.stream, a);
-            else hipLaunchKernelGGL((k_last_inv<T, PPT, false, true>), g, b, dyn, p.stream, a);
-        } else {
-            if (gen) hipLaunchKernelGGL((k_last_inv<T, PPT, true, false>), g, b, dyn, p.stream, a);
-            else hipLaunchKernelGGL((k_last_inv<T, PPT, false, false>), g, b, dyn, p.stream, a);
-        }
-    } else {
-        if (a.use_axpy) {
-            if (gen) hipLaunchKernelGGL((k_last_fwd<T, PPT, true, true>), g, b, dyn, p.stream, a);
-            else hipLaunchKernelGGL((k_last_fwd<T, PPT, false, true>), g, b, dyn, p.stream, a);
-        } else {
-            if (gen) hipLaunchKernelGGL((k_last_fwd<T, PPT, true, false>), g, b, dyn, p.stream, a);
-            else hipLaunchKernelGGL((k_last_fwd<T, PPT, false, false>), g, b, dyn, p.stream, a);
-        }
-    }
+    const bool upd = inverse && fa.p_upd != nullptr;
+    if (upd && (fa.u_upd == nullptr || fa.state == nullptr))
+        return set_error(FEH_EINVAL, "fused CG update needs p, u and the CG state");
+    auto go = [&](auto tile) -> int {
+        constexpr int PP = decltype(tile)::value;
+        size_t dyn;
+        if (lds_of_pass<T>(gen, a.D * RR * nc, a.nlast, &a.lbuf, &dyn, PP) > kLdsPerWorkgroup)
+            return set_error(FEH_ENOTSUP, "last axis too long for the LDS transform");
+        auto run = [&](auto kernel) { hipLaunchKernelGGL(kernel, g, b, dyn, p.stream, a); };
+        with_gen(a.ax, [&](auto gl) {
+            constexpr int G = decltype(gl)::value;
+            if (upd && fa.u_f64) run(k_last_inv<T, PP, G, true, double>);
+            else if (upd) run(k_last_inv<T, PP, G, true>);
+            else if (inverse) run(k_last_inv<T, PP, G, false>);
+            else if (a.use_axpy) run(k_last_fwd<T, PP, G, true>);
+            else run(k_last_fwd<T, PP, G, false>);
+        });
+        return FEH_OK;
+    };
+    CK(small ? go(std::integral_constant<int, ppt<T, true>()>{}) : go(std::integral_constant<int, PPT>{}));
     return hip_check(hipGetLastError(), "last-axis fft launch");
+}
+
+// k_middle over a's pencils, with the full or the small tile
+template <typename T>
+int launch_middle_tile(const feh_plan &p, FK<T> &a, bool small, bool inverse, const char *what) {
+    const bool gen = !pow2_len(a.ax.n);
+    auto go = [&](auto tile) -> int {
+        constexpr int PP = decltype(tile)::value;
+        size_t dyn;
+        if (lds_of_pass<T>(gen, a.PB * a.n1, a.n1, &a.lbuf, &dyn, PP) > kLdsPerWorkgroup)
+            return set_error(FEH_ENOTSUP, "axis too long for the LDS transform");
+        auto run = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(a.total), dim3(kFftThreads), dyn, p.stream, a, inverse ? 1 : 0);
+        };
+        with_gen(a.ax, [&](auto gl) { run(k_middle<T, PP, decltype(gl)::value>); });
+        return hip_check(hipGetLastError(), what);
+    };
+    return small ? go(std::integral_constant<int, ppt<T, true>()>{}) : go(std::integral_constant<int, ppt<T>()>{});
 }
 
 template <typename T>
@@ -1998,6 +2185,8 @@ int middle_t(const feh_plan &p, const FftArgs &fa, bool inverse) {
     if (PB > 32) PB = 32;
     if (p.tune_pb_mid > 0 && p.tune_pb_mid < PB) PB = p.tune_pb_mid;
     if (PB > inner) PB = (int)inner;
+    const bool small = p.tune_pb_mid == 0 && small_tile(inner, PB, std::min(PB, ppt<T, true>() * kFftThreads / a.n1),
+                                                        (long long)a.n0 * p.L, &PB);
     a.PB = PB;
     a.d_PB = FastDiv::make((uint32_t)PB);
     a.inner_total = inner;
@@ -2024,16 +2213,7 @@ int middle_t(const feh_plan &p, const FftArgs &fa, bool inverse) {
         }
         return hip_check(hipGetLastError(), "middle-axis fft launch");
     }
-    size_t dyn;
-    if (lds_of_pass<T>(!pow2_len(a.ax.n), PB * a.n1, a.n1, &a.lbuf, &dyn) > kLdsPerWorkgroup)
-        return set_error(FEH_ENOTSUP, "middle axis too long for the LDS transform");
-    if (pow2_len(a.ax.n))
-        hipLaunchKernelGGL((k_middle<T, PPT, false>), dim3(a.total), dim3(kFftThreads), dyn, p.stream, a,
-                           inverse ? 1 : 0);
-    else
-        hipLaunchKernelGGL((k_middle<T, PPT, true>), dim3(a.total), dim3(kFftThreads), dyn, p.stream, a,
-                           inverse ? 1 : 0);
-    return hip_check(hipGetLastError(), "middle-axis fft launch");
+    return launch_middle_tile<T>(p, a, small, inverse, "middle-axis fft launch");
 }
 
 // c2c along axis 0 of a spectrum with fa.comps components, no k-solve: the
@@ -2052,6 +2232,7 @@ int first_plain_t(const feh_plan &p, const FftArgs &fa, bool inverse) {
     if (PB < 1) return set_error(FEH_ENOTSUP, "first axis too long for the LDS transform");
     if (PB > 32) PB = 32;
     if (PB > inner) PB = (int)inner;
+    const bool small = small_tile(inner, PB, std::min(PB, ppt<T, true>() * kFftThreads / len), p.L, &PB);
     a.PB = PB;
     a.d_PB = FastDiv::make((uint32_t)PB);
     a.inner_total = inner;
@@ -2059,16 +2240,24 @@ int first_plain_t(const feh_plan &p, const FftArgs &fa, bool inverse) {
     a.n0 = 1;     // one outer slice per load case
     a.nblk = (int)((inner + PB - 1) / PB);
     a.total = a.nblk * p.L;
-    size_t dyn;
-    if (lds_of_pass<T>(!pow2_len(a.ax.n), PB * len, len, &a.lbuf, &dyn) > kLdsPerWorkgroup)
-        return set_error(FEH_ENOTSUP, "first axis too long for the LDS transform");
-    if (pow2_len(a.ax.n))
-        hipLaunchKernelGGL((k_middle<T, PPT, false>), dim3(a.total), dim3(kFftThreads), dyn, p.stream, a,
-                           inverse ? 1 : 0);
-    else
-        hipLaunchKernelGGL((k_middle<T, PPT, true>), dim3(a.total), dim3(kFftThreads), dyn, p.stream, a,
-                           inverse ? 1 : 0);
-    return hip_check(hipGetLastError(), "first-axis fft launch");
+    return launch_middle_tile<T>(p, a, small, inverse, "first-axis fft launch");
+}
+
+// The CG's first-axis pass reads its inverses from the table.
+bool first_by_table(const feh_plan &p) { return first_per_load_case(p) || p.metric != 0 || p.tune_first_perlc == 0; }
+
+// Whether the CG's run-time first-axis pass takes the small tile, and its
+// pencils (at least a quarter of the default: the partial sums have one slot a
+// pencil block of that size).  *PB: the full tile's pencils.
+bool first_small_pencils(const feh_plan &p, int *PB) {
+    if (p.tune_pb_first != 0 || !first_by_table(p) || first_ct_pencils(p)) return false;
+    const int points = (p.prec == FEH_FP32 ? ppt<float, true>() : ppt<double, true>()) * kFftThreads;
+    const long long inner = p.dim == 3 ? p.n[1] * p.nh : p.nh;
+    const int least = std::min(*PB, std::max(1, first_pencils_default(p) / 4));
+    int take;
+    if (!small_tile(inner, *PB, std::min(*PB, points / ((int)p.n[0] * p.dim)), p.L, &take)) return false;
+    *PB = std::max(take, least);
+    return true;
 }
 
 template <typename T, int DIM>
@@ -2089,6 +2278,7 @@ int first_t(const feh_plan &p, const FftArgs &fa, int mode) {
     // a grid with fewer pencils than one block
     if (ctpb > 0) PB = ctpb;
     else if (PB > a.inner_total) PB = (int)a.inner_total;
+    const bool small = mode == 0 && fa.unit_volume && first_small_pencils(p, &PB);
     a.PB = PB;
     a.d_PB = FastDiv::make((uint32_t)PB);
     a.nbd = FastDiv::make((uint32_t)(PB * DIM));
@@ -2101,12 +2291,11 @@ int first_t(const feh_plan &p, const FftArgs &fa, int mode) {
     // 160^3 44.0 -> 37.0; FP64 2D: 151^2 25.1 -> 13.4, 300^2 5.2 -> 3.7,
     // 900^2 9.9 -> 10.0).
     const bool table = mode == 0 && fa.unit_volume;
-    const bool perlc = first_per_load_case(p) || p.metric != 0 || (table && p.tune_first_perlc == 0);
+    const bool perlc = table ? first_by_table(p) : first_per_load_case(p);
     a.total = perlc ? a.nblk * p.L : a.nblk;  // one block per (load case, pencils) or per pencils
     dim3 g(a.total), b(kFftThreads);
-    const bool gen = !pow2_len(a.ax.n);
     const size_t dyn = ((a.n0 * sizeof(Cx<T>) + 15) / 16) * 16 + (mode == 0 ? 4 * (size_t)PB * sizeof(Cx<double>) : 0);
-    if (PPT * kFftThreads * sizeof(Cx<T>) + (kFftThreads / 64) * sizeof(double) + dyn > kLdsPerWorkgroup)
+    if ((small ? ppt<T, true>() : PPT) * kFftThreads * sizeof(Cx<T>) + (kFftThreads / 64) * sizeof(double) + dyn > kLdsPerWorkgroup)
         return set_error(FEH_ENOTSUP, "first axis too long for the LDS transform");
     // the CG's fused pass (element volume relative to the voxel) reads the
     // (B^*B)^-1 table, built here on the first use for this workspace and
@@ -2135,26 +2324,20 @@ int first_t(const feh_plan &p, const FftArgs &fa, int mode) {
         }
         return hip_check(hipGetLastError(), "first-axis fft launch");
     }
-#define FEH_FIRST(M, G)                                                                                   \
-    do {                                                                                                  \
-        if (perlc) hipLaunchKernelGGL((k_first<T, PPT, DIM, M, G, true, false>), g, b, dyn, p.stream, a); \
-        else hipLaunchKernelGGL((k_first<T, PPT, DIM, M, G, false, false>), g, b, dyn, p.stream, a);      \
-    } while (0)
-    switch (mode * 2 + (gen ? 1 : 0)) {
-    case 0:
-        if (tab) hipLaunchKernelGGL((k_first<T, PPT, DIM, 0, false, true, true>), g, b, dyn, p.stream, a);
-        else FEH_FIRST(0, false);
-        break;
-    case 1:
-        if (tab) hipLaunchKernelGGL((k_first<T, PPT, DIM, 0, true, true, true>), g, b, dyn, p.stream, a);
-        else FEH_FIRST(0, true);
-        break;
-    case 2: FEH_FIRST(1, false); break;
-    case 3: FEH_FIRST(1, true); break;
-    case 4: FEH_FIRST(2, false); break;
-    default: FEH_FIRST(2, true); break;
-    }
-#undef FEH_FIRST
+    auto run = [&](auto kernel) { hipLaunchKernelGGL(kernel, g, b, dyn, p.stream, a); };
+    with_gen(a.ax, [&](auto gl) {
+        constexpr int G = decltype(gl)::value;
+        auto layouts = [&](auto m) {
+            constexpr int M = decltype(m)::value;
+            if (perlc) run(k_first<T, PPT, DIM, M, G, true, false>);
+            else run(k_first<T, PPT, DIM, M, G, false, false>);
+        };
+        if (small) run(k_first<T, ppt<T, true>(), DIM, 0, G, true, true>);
+        else if (tab) run(k_first<T, PPT, DIM, 0, G, true, true>);
+        else if (mode == 0) layouts(std::integral_constant<int, 0>{});
+        else if (mode == 1) layouts(std::integral_constant<int, 1>{});
+        else layouts(std::integral_constant<int, 2>{});
+    });
     return hip_check(hipGetLastError(), "first-axis fft launch");
 }
 
@@ -2165,12 +2348,13 @@ int first_dispatch(const feh_plan &p, const FftArgs &fa, int mode) {
 
 }  // namespace
 
-// Default first-axis layout: one workgroup per (load case, pencil block) when
-// the axis length is a power of two.  That variant forms the inverses again per
-// load case but fits 3 waves per SIMD (FP32; 2 in FP64, bound by LDS) against 2
-// (FP32) or 1 (FP64) for the register-cached variant, and runs faster at every
-// measured size.  General lengths keep the cached variant (both hold about as
-// many registers there).
+// Default first-axis layout of the passes that form their inverses: one
+// workgroup per (load case, pencil block) when the axis length is a power of
+// two.  That variant forms the inverses again per load case but fits 3 waves
+// per SIMD (FP32; 2 in FP64, bound by LDS) against 2 (FP32) or 1 (FP64) for
+// the register-cached variant, and runs faster at every measured size.
+// General lengths keep the cached variant (both hold about as many registers
+// there).
 bool first_per_load_case(const feh_plan &p) {
     if (p.tune_first_perlc != 0) return p.tune_first_perlc > 0;
     return pow2_len((int)p.n[0]);
@@ -2207,6 +2391,7 @@ int first_num_parts(const feh_plan &p) {
     if (const int ct = first_ct_pencils(p)) PB = ct;  // the CG's fused pass
     const long long inner = p.dim == 3 ? p.n[1] * p.nh : p.nh;
     if (PB > inner) PB = (int)inner;
+    (void)first_small_pencils(p, &PB);
     return (int)((inner + PB - 1) / PB);
 }
 
