@@ -628,6 +628,7 @@ int feh_plan_set_workspace(feh_plan *plan, void *dev_ptr, size_t bytes) {
         if (reinterpret_cast<uintptr_t>(dev_ptr) % 256 != 0) return set_error(FEH_EINVAL, "workspace must be 256-byte aligned");
         plan->ws = static_cast<char *>(dev_ptr);
         plan->ws_bytes = bytes;
+        plan->minv_ws = nullptr;  // also when the address is the last one: the buffer may have been used since
         plan->material_set = false;
         plan->solved = false;
         plan->field_nu = -2.0;
@@ -1541,6 +1542,7 @@ int feh_solve_noalloc(feh_plan *plan, const void *lambda_dev, const void *mu_dev
         const double own_nu = p.field_nu;
         p.ws = ws;
         p.ws_bytes = kStaticScratchBytes;
+        p.minv_ws = nullptr;  // other plans use the array between the calls
         int rc = upload_tables(p);
         if (rc == FEH_OK) {
             int *flag = p.ptr<int>(p.off_flag);
@@ -1556,6 +1558,7 @@ int feh_solve_noalloc(feh_plan *plan, const void *lambda_dev, const void *mu_dev
         }
         p.ws = own_ws;
         p.ws_bytes = own_bytes;
+        p.minv_ws = nullptr;
         p.material_set = own_material;
         p.solved = own_solved;
         p.field_nu = own_nu;
