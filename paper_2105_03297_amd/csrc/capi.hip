@@ -701,7 +701,8 @@ int feh_set_material_field(feh_plan *plan, const void *E_dev, double nu) {
 // solve stages: set-up (right-hand side, first search direction), CG loop,
 // finalisation (pending u update, post-processing, host outputs)
 // ---------------------------------------------------------------------------
-static int solve_begin(feh_plan &p, const double *Ebar_host, double tol, int max_iter, const void *u0_dev) {
+// Checks the arguments of a solve and uploads Ebar.
+static int solve_inputs(feh_plan &p, const double *Ebar_host, double tol, int max_iter) {
     if (!Ebar_host) return set_error(FEH_EINVAL, "null Ebar");
     if (!(tol >= 0.0) || !std::isfinite(tol)) return set_error(FEH_EINVAL, "tol must be finite and >= 0");
     p.solved = false;
@@ -721,13 +722,17 @@ static int solve_begin(feh_plan &p, const double *Ebar_host, double tol, int max
     CK(hip_check(hipMemcpyAsync(ebar_dev, eb.data(), eb.size() * sizeof(double), hipMemcpyHostToDevice, p.stream),
                  "upload Ebar"));
     // the host vector must outlive the asynchronous copy
-    CK(hip_check(hipStreamSynchronize(p.stream), "upload Ebar"));
+    return hip_check(hipStreamSynchronize(p.stream), "upload Ebar");
+}
+
+static int solve_begin(feh_plan &p, const double *Ebar_host, double tol, int max_iter, const void *u0_dev) {
+    CK(solve_inputs(p, Ebar_host, tol, max_iter));
     LcState *st = p.ptr<LcState>(p.off_state);
     double *part = p.ptr<double>(p.off_part);
-    const size_t nvec = (size_t)p.L * D * p.N;
+    const size_t nvec = (size_t)p.L * p.dim * p.N;
     CK(launch_init_state(p, st, p.L));
     StencilArgs sa;
-    sa.Ebar = ebar_dev;
+    sa.Ebar = p.ptr<double>(p.off_ebar);
     sa.unit_volume = true;
     if (u0_dev) {
         CK(launch_aos_to_soa(p, u0_dev, p.ws + p.off_u));
@@ -837,6 +842,11 @@ static int any_active(feh_plan *const *plans, int n, std::vector<std::vector<LcS
 static int solve_all(feh_plan &p, const double *Ebar_host, double tol, int max_iter, const void *u0_dev, void *u_dev,
                      void *strain_dev, void *stress_dev, double *stress_mean_host, double *energy_host,
                      feh_report *report_host) {
+    if (!u0_dev && small_solve_ok(p, false)) {
+        CK(solve_inputs(p, Ebar_host, tol, max_iter));
+        CK(launch_small_solve(p, tol, max_iter));
+        return solve_end(p, u_dev, strain_dev, stress_dev, stress_mean_host, energy_host, report_host);
+    }
     CK(solve_begin(p, Ebar_host, tol, max_iter, u0_dev));
     LcState *st = p.ptr<LcState>(p.off_state);
     std::vector<std::vector<LcState>> hs(1);
@@ -1182,6 +1192,7 @@ int feh_plan_autotune(feh_plan *plan, int reps) {
         CK(check_plan(plan, false));
         feh_plan &p = *plan;
         if (reps < 1) reps = 3;
+        p.schedule_set = true;
         const int D = p.dim;
         // transform zeros: the timing does not depend on the values
         const size_t nvec = (size_t)p.L * D * p.N;
@@ -1330,6 +1341,7 @@ int feh_plan_set_tuning(feh_plan *plan, const int *values, int n_values) {
             ct = values[i++];
             if (ct != 0 && ct != 1) return set_error(FEH_EINVAL, "compile-time transform flag must be 0 or 1");
         }
+        p.schedule_set = true;
         for (int a = 0; a < 3; ++a) p.fft[a] = ax[a];
         p.tune_ct = ct;
         p.tune_rr_last = rr;

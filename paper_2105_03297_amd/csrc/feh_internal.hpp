@@ -152,6 +152,7 @@ struct feh_plan {
     int tune_stencil_vy = 0;            // 3D stencil tile rows (8 or 16; 0: default)
     int tune_first_perlc = 0;           // axis-0 pass: 1 one workgroup per load case, -1 all load cases, 0 default
     int tune_ct = 1;                    // 1: compile-time transforms where the shape has one, 0: run-time passes only
+    bool schedule_set = false;          // by feh_plan_set_tuning or feh_plan_autotune
     bool solved = false;                // off_u holds the fluctuations of the last feh_solve
     // set while a NodalScope is in place:
     bool u_f64 = false;                 // off_u holds doubles whatever prec
@@ -256,6 +257,7 @@ struct FftArgs {
 };
 
 int launch_forward_last(const feh_plan &p, const FftArgs &a);   // r2c along the last axis
+int launch_inverse_table(const feh_plan &p);  // (B^*B)^-1 in plain order (blocks of one pencil) at off_minv
 int launch_middle(const feh_plan &p, const FftArgs &a, bool inverse);  // c2c axis 1 (3D)
 int launch_first_fused(const feh_plan &p, const FftArgs &a);    // c2c axis 0 fwd, k-solve, inv
 int launch_first(const feh_plan &p, const FftArgs &a, bool inverse);  // c2c axis 0 only
@@ -349,6 +351,21 @@ int launch_nodal_residual(const feh_plan &p, const NodalOp &op, void *r);  // |P
 int launch_nodal_step(const feh_plan &p, const NodalOp &op, double *u, const double *du, const int *mask);
 int launch_nodal_post(const feh_plan &p, const NodalOp &op, void *F, void *P);  // rows: sums of P_ic
 int launch_nodal_reduce(const feh_plan &p, const double *partial, int nq, int nparts, double *out, double scale);
+
+// Grids that fit one CU (kern_small.hip): the whole solve of every load case
+// from u = 0 in one launch.  Ebar at off_ebar; u and the CG states come back
+// at off_u and off_state, nothing pending.
+bool small_solve_ok(const feh_plan &p, bool finite);
+int launch_small_solve(const feh_plan &p, double tol, int max_iter);
+struct SmallFinite {
+    int n_steps, max_newton, max_cg;
+    double newton_tol, equil_tol, cg_tol;
+    const double *Fbar_end;  // device [L][D][D]
+    double *fbar;            // device: Fbar of the last load step
+    double *u;               // device [L][D][N]: displacement fluctuation
+    double *out;             // device [L][5]: newton, cg, status, rel_equilibrium, rel_increment
+};
+int launch_small_finite(const feh_plan &p, int kind, const SmallFinite &f);
 
 // partial-sum sizes
 int stencil_num_parts(const feh_plan &p);

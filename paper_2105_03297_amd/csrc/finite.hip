@@ -672,6 +672,25 @@ int fs_solve_nodal(feh_plan &p, int kind, char *work, const NLayout &Lo, const d
     out.rel_eq.assign(L, 0.0);
     out.rel_inc.assign(L, 0.0);
     std::vector<double> fb(L * DD), h;
+    if (small_solve_ok(p, true)) {
+        // one launch; its outputs in the partial sums, which it does not use
+        CK(hip_check(hipMemcpyAsync(sums, Fbar_host, L * DD * sizeof(double), hipMemcpyHostToDevice, p.stream), "upload Fbar"));
+        const SmallFinite f{prm.n_steps, prm.max_newton, prm.max_cg, prm.newton_tol, prm.equil_tol, prm.cg_tol, sums, fbar, u, part};
+        CK(launch_small_finite(p, kind, f));
+        h.resize(5 * L);
+        CK(hip_check(hipMemcpyAsync(h.data(), part, h.size() * sizeof(double), hipMemcpyDeviceToHost, p.stream), "read outcome"));
+        CK(hip_check(hipStreamSynchronize(p.stream), "finite strain"));
+        for (int l = 0; l < L; ++l) {
+            out.newton[l] = (int)h[5 * l];
+            out.cg[l] = (int)h[5 * l + 1];
+            out.status[l] = (int)h[5 * l + 2];
+            out.rel_eq[l] = h[5 * l + 3];
+            out.rel_inc[l] = h[5 * l + 4];
+        }
+        CK(launch_nodal_post(p, op, Fout, Pout));
+        CK(launch_nodal_reduce(p, part, L * DD, np, sums, 1.0 / ((double)p.N * points_of(kind, D))));
+        return read(out.pmean, L * DD);
+    }
     std::vector<int> done(L), hmask(L);
     std::vector<LcState> hs(L);
     const bool rs = cg_residual_spectral(p);

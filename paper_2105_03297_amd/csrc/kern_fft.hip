@@ -18,26 +18,12 @@
 #include <algorithm>
 #include <type_traits>
 
-#include "device_common.hpp"
+#include "fft_butterflies.hpp"
 
 namespace feh {
 namespace {
 
 constexpr int kFftThreads = 256;
-
-template <typename T>
-__device__ __forceinline__ Cx<T> mul_mi(Cx<T> a) { return {a.y, -a.x}; }  // a * (-i)
-template <typename T>
-__device__ __forceinline__ Cx<T> mul_pi(Cx<T> a) { return {-a.y, a.x}; }  // a * (+i)
-template <typename T>
-__device__ __forceinline__ Cx<T> cscale(Cx<T> a, T s) { return {a.x * s, a.y * s}; }
-
-template <typename T>
-__device__ __forceinline__ Cx<T> twid(const Cx<T> *tw, int tws, int e, bool inv) {
-    Cx<T> w = tw[e * tws];
-    if (inv) w.y = -w.y;
-    return w;
-}
 
 // Dynamic LDS holds the twiddle table of the transformed axis (and, in the
 // fused first-axis pass, the phase factors of the block's inner wavevector
@@ -84,128 +70,6 @@ template <typename T>
 __device__ __forceinline__ void stage(T *dst, const T *src, int count) {
     for (int i = threadIdx.x; i < count; i += kFftThreads) dst[i] = src[i];
 }
-
-// In-place DFT of length R on registers: x[d] <- sum_c x[c] exp(-+2 pi i c d / R).
-template <typename T, int R>
-struct Dft {
-    // generic radix (7, 11, 13): roots from the table of the full length n
-    static __device__ __forceinline__ void run(Cx<T> (&x)[R], bool inv, const Cx<T> *tw, int tws, int n) {
-        Cx<T> y[R];
-        const int step = n / R;
-        #pragma unroll
-        for (int d = 0; d < R; ++d) {
-            Cx<T> s = x[0];
-            #pragma unroll
-            for (int c = 1; c < R; ++c) s = cadd(s, cmul(x[c], twid(tw, tws, ((c * d) % R) * step, inv)));
-            y[d] = s;
-        }
-        #pragma unroll
-        for (int d = 0; d < R; ++d) x[d] = y[d];
-    }
-};
-
-template <typename T>
-struct Dft<T, 2> {
-    static __device__ __forceinline__ void run(Cx<T> (&x)[2], bool, const Cx<T> *, int, int) {
-        const Cx<T> a = x[0];
-        x[0] = cadd(a, x[1]);
-        x[1] = csub(a, x[1]);
-    }
-};
-
-template <typename T>
-struct Dft<T, 3> {
-    static __device__ __forceinline__ void run(Cx<T> (&x)[3], bool inv, const Cx<T> *, int, int) {
-        const T s3 = T(0.86602540378443864676);
-        const Cx<T> t1 = cadd(x[1], x[2]), t2 = csub(x[1], x[2]);
-        const Cx<T> a = {x[0].x - T(0.5) * t1.x, x[0].y - T(0.5) * t1.y};
-        const Cx<T> b = cscale(t2, s3);
-        x[0] = cadd(x[0], t1);
-        if (!inv) {
-            x[1] = cadd(a, mul_mi(b));
-            x[2] = cadd(a, mul_pi(b));
-        } else {
-            x[1] = cadd(a, mul_pi(b));
-            x[2] = cadd(a, mul_mi(b));
-        }
-    }
-};
-
-template <typename T>
-__device__ __forceinline__ void dft4(Cx<T> &x0, Cx<T> &x1, Cx<T> &x2, Cx<T> &x3, bool inv) {
-    const Cx<T> a = cadd(x0, x2), b = csub(x0, x2), c = cadd(x1, x3), d = csub(x1, x3);
-    x0 = cadd(a, c);
-    x2 = csub(a, c);
-    if (!inv) {
-        x1 = cadd(b, mul_mi(d));
-        x3 = cadd(b, mul_pi(d));
-    } else {
-        x1 = cadd(b, mul_pi(d));
-        x3 = cadd(b, mul_mi(d));
-    }
-}
-
-template <typename T>
-struct Dft<T, 4> {
-    static __device__ __forceinline__ void run(Cx<T> (&x)[4], bool inv, const Cx<T> *, int, int) {
-        dft4(x[0], x[1], x[2], x[3], inv);
-    }
-};
-
-template <typename T>
-struct Dft<T, 5> {
-    static __device__ __forceinline__ void run(Cx<T> (&x)[5], bool inv, const Cx<T> *, int, int) {
-        const T c1 = T(0.30901699437494742410), c2 = T(-0.80901699437494742410);
-        const T s1 = T(0.95105651629515357212), s2 = T(0.58778525229247312917);
-        const Cx<T> t1 = cadd(x[1], x[4]), t2 = cadd(x[2], x[3]);
-        const Cx<T> t3 = csub(x[1], x[4]), t4 = csub(x[2], x[3]);
-        const Cx<T> a1 = {x[0].x + c1 * t1.x + c2 * t2.x, x[0].y + c1 * t1.y + c2 * t2.y};
-        const Cx<T> a2 = {x[0].x + c2 * t1.x + c1 * t2.x, x[0].y + c2 * t1.y + c1 * t2.y};
-        const Cx<T> b1 = {s1 * t3.x + s2 * t4.x, s1 * t3.y + s2 * t4.y};
-        const Cx<T> b2 = {s2 * t3.x - s1 * t4.x, s2 * t3.y - s1 * t4.y};
-        x[0] = cadd(x[0], cadd(t1, t2));
-        if (!inv) {
-            x[1] = cadd(a1, mul_mi(b1));
-            x[4] = cadd(a1, mul_pi(b1));
-            x[2] = cadd(a2, mul_mi(b2));
-            x[3] = cadd(a2, mul_pi(b2));
-        } else {
-            x[1] = cadd(a1, mul_pi(b1));
-            x[4] = cadd(a1, mul_mi(b1));
-            x[2] = cadd(a2, mul_pi(b2));
-            x[3] = cadd(a2, mul_mi(b2));
-        }
-    }
-};
-
-template <typename T>
-struct Dft<T, 8> {
-    static __device__ __forceinline__ void run(Cx<T> (&x)[8], bool inv, const Cx<T> *, int, int) {
-        const T h = T(0.70710678118654752440);
-        Cx<T> e0 = x[0], e1 = x[2], e2 = x[4], e3 = x[6];
-        Cx<T> o0 = x[1], o1 = x[3], o2 = x[5], o3 = x[7];
-        dft4(e0, e1, e2, e3, inv);
-        dft4(o0, o1, o2, o3, inv);
-        // o_d *= W8^d, W8 = exp(-+ i pi / 4)
-        if (!inv) {
-            o1 = {h * (o1.x + o1.y), h * (o1.y - o1.x)};
-            o2 = mul_mi(o2);
-            o3 = {h * (o3.y - o3.x), -h * (o3.x + o3.y)};
-        } else {
-            o1 = {h * (o1.x - o1.y), h * (o1.x + o1.y)};
-            o2 = mul_pi(o2);
-            o3 = {-h * (o3.x + o3.y), h * (o3.x - o3.y)};
-        }
-        x[0] = cadd(e0, o0);
-        x[4] = csub(e0, o0);
-        x[1] = cadd(e1, o1);
-        x[5] = csub(e1, o1);
-        x[2] = cadd(e2, o2);
-        x[6] = csub(e2, o2);
-        x[3] = cadd(e3, o3);
-        x[7] = csub(e3, o3);
-    }
-};
 
 // One Stockham pass over nb batches stored interleaved: element j of batch b
 // at buf[j * nb + b].  Threads take butterflies batch-fastest so that a
@@ -332,27 +196,6 @@ __device__ __forceinline__ void direct_pass(Cx<T> *buf, int nb, int n, const Pas
     }
     __syncthreads();
 }
-
-// Matrix-core tile D = A B + C of 16 rows, 16 columns and 4 inner steps (one
-// wavefront): lane l holds A(l % 16, l / 16) and B(l / 16, l % 16).
-template <typename T>
-struct Mfma;
-template <>
-struct Mfma<double> {
-    typedef double Acc __attribute__((ext_vector_type(4)));
-    static __device__ __forceinline__ Acc run(double a, double b, Acc c) {
-        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-    }
-    static __device__ __forceinline__ int row(int lane, int r) { return 4 * r + (lane >> 4); }  // of c[r]
-};
-template <>
-struct Mfma<float> {
-    typedef float Acc __attribute__((ext_vector_type(4)));
-    static __device__ __forceinline__ Acc run(float a, float b, Acc c) {
-        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-    }
-    static __device__ __forceinline__ int row(int lane, int r) { return 4 * (lane >> 4) + r; }
-};
 
 // Tiles of prime_pass a wavefront may hold: what the accumulators of a
 // workgroup's PPT points a thread need, with room for rounding up.
@@ -2260,6 +2103,31 @@ bool first_small_pencils(const feh_plan &p, int *PB) {
     return true;
 }
 
+// The table for a's block size and slot order, unless the workspace has it.
+template <typename T, int DIM>
+int ensure_table(const feh_plan &p, const FK<T> &a) {
+    if (p.minv_ws == p.ws && p.minv_pb == a.PB && p.minv_q == a.minv_q && p.minv_metric == p.metric) return FEH_OK;
+    hipLaunchKernelGGL((k_first_table<T, DIM>), dim3(a.nblk), dim3(kFftThreads), 0, p.stream, a);
+    CK(hip_check(hipGetLastError(), "inverse table launch"));
+    p.minv_ws = p.ws;
+    p.minv_pb = a.PB;
+    p.minv_q = a.minv_q;
+    p.minv_metric = p.metric;
+    return FEH_OK;
+}
+
+template <typename T, int DIM>
+int plain_table(const feh_plan &p) {
+    FftArgs fa;
+    fa.unit_volume = true;
+    FK<T> a = base_args<T>(p, fa);
+    a.minv = p.ptr<T>(p.off_minv);
+    a.PB = 1;
+    a.d_PB = FastDiv::make(1);
+    a.nblk = (int)a.inner_total;
+    return ensure_table<T, DIM>(p, a);
+}
+
 template <typename T, int DIM>
 int first_t(const feh_plan &p, const FftArgs &fa, int mode) {
     constexpr int PPT = ppt<T>();
@@ -2305,15 +2173,8 @@ int first_t(const feh_plan &p, const FftArgs &fa, int mode) {
         a.minv = p.ptr<T>(p.off_minv);
         // the compile-time pass reads the table with lane-interleaved slots
         a.minv_q = ctpb > 0 ? 16 / (int)sizeof(T) : 0;
-        if (p.minv_ws != p.ws || p.minv_pb != PB || p.minv_q != a.minv_q || p.minv_metric != p.metric) {
-            hipLaunchKernelGGL((k_first_table<T, DIM>), dim3(a.nblk), b, 0, p.stream, a);
-            const int rc = hip_check(hipGetLastError(), "inverse table launch");
-            if (rc != FEH_OK) return rc;
-            p.minv_ws = p.ws;
-            p.minv_pb = PB;
-            p.minv_q = a.minv_q;
-            p.minv_metric = p.metric;
-        }
+        const int rc = ensure_table<T, DIM>(p, a);
+        if (rc != FEH_OK) return rc;
     }
     if (ctpb > 0) {
         switch (a.n0) {
@@ -2393,6 +2254,11 @@ int first_num_parts(const feh_plan &p) {
     if (PB > inner) PB = (int)inner;
     (void)first_small_pencils(p, &PB);
     return (int)((inner + PB - 1) / PB);
+}
+
+int launch_inverse_table(const feh_plan &p) {
+    if (p.prec == FEH_FP64) return p.dim == 3 ? plain_table<double, 3>(p) : plain_table<double, 2>(p);
+    return p.dim == 3 ? plain_table<float, 3>(p) : plain_table<float, 2>(p);
 }
 
 int launch_forward_last(const feh_plan &p, const FftArgs &a) {
