@@ -160,6 +160,8 @@ static void layout(feh_plan &p) {
     }
     const int fp = (int)((inner0 + pbmin - 1) / pbmin);
     p.part_stride = (size_t)(sp > fp ? sp : fp);
+    // the post-processing's sums often take more: the same buffer, more room a load case
+    p.part_stride = std::max(p.part_stride, (size_t)post_num_slots(p) * post_num_parts(p) / p.L);
     p.off_part = take(partial_bytes(p));
     p.off_state = take((size_t)p.L * sizeof(LcState));
     p.off_flag = take(256);

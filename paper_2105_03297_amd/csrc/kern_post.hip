@@ -352,14 +352,14 @@ struct MTile<2> {
 };
 
 struct MarchGeom {
-    int nty, ntz, nchunk;
+    int nty, ntz, nchunk, chunk;
 };
 
 template <int DIM>
 MarchGeom march_geom(const feh_plan &p) {
     using TL = MTile<DIM>;
     const int n0 = (int)p.n[0], n1 = DIM == 3 ? (int)p.n[1] : 1, n2 = (int)p.n[DIM - 1];
-    return MarchGeom{(n1 + TL::VY - 1) / TL::VY, (n2 + TL::VZ - 1) / TL::VZ, (n0 + kMarchChunk - 1) / kMarchChunk};
+    return MarchGeom{(n1 + TL::VY - 1) / TL::VY, (n2 + TL::VZ - 1) / TL::VZ, (n0 + kMarchChunk - 1) / kMarchChunk, kMarchChunk};
 }
 
 // In-plane offsets of the corner nodes of a voxel column (corner
@@ -589,7 +589,7 @@ __global__ __launch_bounds__(kThreads) void k_post_march(PK<T, S> a, MarchGeom g
     const int y = ty_t * TL::VY + (DIM == 3 ? (int)threadIdx.x / TL::VZ : 0);
     const int z = tz_t * TL::VZ + (int)threadIdx.x % TL::VZ;
     const bool inside = (DIM == 2 || y < a.n1) && z < a.n2;
-    const int x0 = ch * kMarchChunk, x1 = min(x0 + kMarchChunk, a.n0);
+    const int x0 = ch * geo.chunk, x1 = min(x0 + geo.chunk, a.n0);
     const uint32_t plane = (uint32_t)a.n1 * (uint32_t)a.n2;
     const long long mo = (long long)b * a.N;
     double Ebl[DIM][DIM];
@@ -870,7 +870,16 @@ static int post_t(const feh_plan &p, const void *u, const double *Ebar, void *st
     a.stress = static_cast<S *>(stress);
     a.partial = partial;
     if (march_ok(p)) {
-        const MarchGeom geo = p.dim == 3 ? march_geom<3>(p) : march_geom<2>(p);
+        MarchGeom geo = p.dim == 3 ? march_geom<3>(p) : march_geom<2>(p);
+        // shorter marches while the chip is part empty and the partial sums
+        // have room (32^2 x 3 load cases: 35 -> POST_FIGURE us)
+        const int room = post_num_parts(p), n0 = (int)p.n[0];
+        while (geo.chunk > 2 && (long long)geo.nty * geo.ntz * geo.nchunk * p.L < 1024) {
+            const int c = geo.chunk / 2, k = (n0 + c - 1) / c;
+            if (geo.nty * geo.ntz * k > room) break;
+            geo.chunk = c;
+            geo.nchunk = k;
+        }
         a.nblk = geo.nty * geo.ntz * geo.nchunk;
         dim3 g(a.nblk * p.G, p.nbatch);
         const bool fields = a.strain || a.stress;

@@ -58,7 +58,7 @@ struct SmallArgs {
     int G;                  // load cases per material
     int n[3], N, rows, nlast, nc, nh, S, even, inner, nspec;
     FastDiv d_N, d_last, d_nh, d_inner, d_D, d_half;
-    int table_lds;
+    int table_lds, mat_lds;  // the table of inverses, the material kept in LDS
     T ih[3], vol;
     double ihd[3], w, invN, tol;
     int max_iter;
@@ -281,14 +281,20 @@ __device__ __forceinline__ int real_at(const SmallArgs<T> &a, int row, int i, in
     return a.even ? 2 * ((row * a.S + (i >> 1)) * DIM + c) + (i & 1) : 2 * ((row * a.S + i) * DIM + c);
 }
 
-// Sum over the workgroup, in every thread.
-__device__ __forceinline__ double all_sum(double v, double *red) {
-    const double s = block_sum<NT>(v, red);
-    if (threadIdx.x == 0) red[NW] = s;
+// Sum over the workgroup, in every thread (fixed order).  One barrier: calls
+// take the two halves of `red` in turn (`turn` flips), so that a wavefront
+// still summing one half is never overtaken by the next call's writes.
+__device__ __forceinline__ double all_sum(double v, double *red, int &turn) {
+    #pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    double *r = red + turn * NW;
+    turn ^= 1;
+    if ((threadIdx.x & 63) == 0) r[threadIdx.x >> 6] = v;
     __syncthreads();
-    const double r = red[NW];
-    __syncthreads();
-    return r;
+    double s = r[0];
+    #pragma unroll
+    for (int i = 1; i < NW; ++i) s += r[i];
+    return s;
 }
 
 // Wavevector slot s = (i0, inner index): its place in W and weight in the
@@ -341,18 +347,21 @@ __device__ __forceinline__ void hooke_column(const Stencil &s, int slot, int c, 
 }
 
 // LDS of a solve: P [D][N], W, R^ (the spectral residual, W's valid points),
-// X (u, or the increment; in U), [F: the displacement], reduction, twiddles,
-// pass lists, table of inverses.  U: the type of X.
+// X (u, or the increment; in U), [F: the displacement], reduction, material,
+// twiddles, pass lists, table of inverses.  U: the type of X.
 template <typename T, typename U, bool FINITE>
 struct Lds {
     T *P;
     Cx<T> *W, *Rh;
     U *X;
     double *F, *red;
+    const T *glam, *gmu;
+    T *lam, *mu;
+    bool in_lds;
     const Cx<T> *tw[2];
     int *pass[2];
     T *tab;
-    __device__ __forceinline__ Lds(const SmallArgs<T> &a) {
+    __device__ __forceinline__ Lds(const SmallArgs<T> &a, long long material) {
         char *o = reinterpret_cast<char *>(small_lds);
         auto take = [&](int bytes) {
             char *at = o;
@@ -364,7 +373,17 @@ struct Lds {
         Rh = reinterpret_cast<Cx<T> *>(take(a.nspec * DIM * (int)sizeof(Cx<T>)));
         X = reinterpret_cast<U *>(take(DIM * a.N * (int)sizeof(U)));
         F = reinterpret_cast<double *>(take(FINITE ? DIM * a.N * 8 : 0));
-        red = reinterpret_cast<double *>(take((NW + 1) * 8));
+        red = reinterpret_cast<double *>(take(2 * NW * 8));
+        glam = a.lam + material;
+        gmu = a.mu + material;
+        in_lds = a.mat_lds != 0;
+        lam = reinterpret_cast<T *>(take(in_lds ? a.N * (int)sizeof(T) : 0));
+        mu = reinterpret_cast<T *>(take(in_lds ? a.N * (int)sizeof(T) : 0));
+        if (in_lds)
+            for (int i = threadIdx.x; i < a.N; i += NT) {
+                lam[i] = glam[i];
+                mu[i] = gmu[i];
+            }
         #pragma unroll
         for (int x = 0; x < DIM; ++x) {
             Cx<T> *t = reinterpret_cast<Cx<T> *>(take(a.n[x] * (int)sizeof(Cx<T>)));
@@ -399,10 +418,16 @@ struct Lds {
     }
 };
 
+template <typename M, typename T>
+__device__ __forceinline__ void material_at(const M &m, unsigned v, T &lam, T &mu) {
+    lam = m.in_lds ? m.lam[v] : m.glam[v];
+    mu = m.in_lds ? m.mu[v] : m.gmu[v];
+}
+
 // STEP false: r^ = spectrum in W; true: r^ -= alpha W.  Then W = z^ = M^-1 r^;
 // returns r.z.
 template <bool STEP, typename T, typename M>
-__device__ __forceinline__ double residual_step(const SmallArgs<T> &a, const M &m, T alpha) {
+__device__ __forceinline__ double residual_step(const SmallArgs<T> &a, const M &m, T alpha, int &turn) {
     constexpr int NC = 4;
     double acc = 0.0;
     for (int s = threadIdx.x; s < a.nspec; s += NT) {
@@ -426,7 +451,7 @@ __device__ __forceinline__ double residual_step(const SmallArgs<T> &a, const M &
         for (int c = 0; c < DIM; ++c) x[c] = z[c];
         acc += wt * d;
     }
-    return all_sum(acc, m.red) * a.invN;  // its barriers also order W for the inverse
+    return all_sum(acc, m.red, turn) * a.invN;  // its barrier also orders W for the inverse
 }
 
 // p = z / N + beta p from the real field in W.
@@ -456,9 +481,9 @@ template <typename T, typename U>
 __global__ __launch_bounds__(NT) void k_small_solve(SmallArgs<T> a) {
     static constexpr Stencil s = make_stencil<DIM, FEH_DERIV_FE>();
     const int l = blockIdx.x;
-    const Lds<T, U, false> m(a);
+    const Lds<T, U, false> m(a, (long long)(l / a.G) * a.N);
     T *w = reinterpret_cast<T *>(m.W);
-    const T *mlam = a.lam + (long long)(l / a.G) * a.N, *mmu = a.mu + (long long)(l / a.G) * a.N;
+    int turn = 0;
     T Eb[DIM][DIM];
     #pragma unroll
     for (int i = 0; i < DIM; ++i)
@@ -469,7 +494,7 @@ __global__ __launch_bounds__(NT) void k_small_solve(SmallArgs<T> a) {
         constexpr bool LOAD = decltype(load)::value;
         double acc = 0.0;
         for (int v = threadIdx.x; v < a.N; v += NT) {
-            const Place<DIM> pl(a.n, (unsigned)v);
+            const Place<DIM> pl(a.n, (unsigned)v, a.d_last.div((uint32_t)v));
             T p[32][DIM];
             if constexpr (LOAD) {
                 #pragma unroll
@@ -484,7 +509,9 @@ __global__ __launch_bounds__(NT) void k_small_solve(SmallArgs<T> a) {
             for (int i = 0; i < DIM; ++i) q[i] = T(0);
             auto column = [&](int slot, int c, T (&col)[DIM]) __attribute__((always_inline)) {
                 const unsigned vo = pl.at(s.vox[slot]);
-                hooke_column<T, LOAD>(s, slot, c, p, a.ih, mlam[vo] * a.vol, mmu[vo] * a.vol, Eb, col);
+                T lam, mu;
+                material_at(m, vo, lam, mu);
+                hooke_column<T, LOAD>(s, slot, c, p, a.ih, lam * a.vol, mu * a.vol, Eb, col);
             };
             #pragma unroll
             for (int k = 0; k < s.nb; ++k) {
@@ -507,7 +534,7 @@ __global__ __launch_bounds__(NT) void k_small_solve(SmallArgs<T> a) {
     apply(std::true_type{});
     __syncthreads();
     forward<T>(a, m.W, m.tw, m.pass);
-    double rho = residual_step<false>(a, m, T(0));
+    double rho = residual_step<false>(a, m, T(0), turn);
     const double ref = rho;
     double relres = 0.0, pq = 0.0, alpha = 0.0, beta = 0.0;
     int iters = 0, status = FEH_OK;
@@ -526,14 +553,14 @@ __global__ __launch_bounds__(NT) void k_small_solve(SmallArgs<T> a) {
         direction<T>(a, m, T(0));
     }
     while (on) {
-        pq = all_sum(apply(std::false_type{}), m.red);
+        pq = all_sum(apply(std::false_type{}), m.red, turn);
         if (!(pq > 0.0) || !isfinite(pq)) {
             status = FEH_EBREAKDOWN;
             break;
         }
         alpha = rho / pq;
         forward<T>(a, m.W, m.tw, m.pass);
-        const double r = residual_step<true>(a, m, T(alpha));
+        const double r = residual_step<true>(a, m, T(alpha), turn);
         for (int e = threadIdx.x; e < DIM * a.N; e += NT) m.X[e] += U(alpha) * U(m.P[e]);
         ++iters;
         if (!isfinite(r)) {
@@ -572,8 +599,9 @@ template <typename T, int KIND>
 __global__ __launch_bounds__(NT) void k_small_finite(SmallArgs<T> a) {
     static constexpr Stencil s = make_stencil<DIM, KIND>();
     const int l = blockIdx.x;
-    const Lds<T, double, true> m(a);
+    const Lds<T, double, true> m(a, 0);
     T *w = reinterpret_cast<T *>(m.W);
+    int turn = 0;
     double sc[DIM], Fb[DIM][DIM];
     #pragma unroll
     for (int x = 0; x < DIM; ++x) sc[x] = a.ihd[x] * (s.half ? 0.5 : 1.0);
@@ -582,7 +610,7 @@ __global__ __launch_bounds__(NT) void k_small_finite(SmallArgs<T> a) {
         constexpr bool TAN = decltype(tan)::value;
         double acc = 0.0;
         for (int v = threadIdx.x; v < a.N; v += NT) {
-            const Place<DIM> pl(a.n, (unsigned)v);
+            const Place<DIM> pl(a.n, (unsigned)v, a.d_last.div((uint32_t)v));
             double u[32][DIM], q[DIM];
             T p[32][DIM];
             lds_nodes<double>(s, m.F, a.N, pl, u);
@@ -591,7 +619,9 @@ __global__ __launch_bounds__(NT) void k_small_finite(SmallArgs<T> a) {
             for (int i = 0; i < DIM; ++i) q[i] = 0.0;
             auto column = [&](int slot, int c, double (&col)[DIM]) __attribute__((always_inline)) {
                 const unsigned vo = pl.at(s.vox[slot]);
-                const double lam = double(a.lam[vo]), mu = double(a.mu[vo]);
+                T tl, tm;
+                material_at(m, vo, tl, tm);
+                const double lam = double(tl), mu = double(tm);
                 const Grad<DIM> f = add<DIM>(point_grad<DIM, double>(s, slot, u, sc), Fb);
                 const double tr = twice_trace<DIM>(f);
                 if constexpr (TAN) {
@@ -620,7 +650,9 @@ __global__ __launch_bounds__(NT) void k_small_finite(SmallArgs<T> a) {
                 if constexpr (TAN) acc += double(p[0][i]) * double(qv);
             }
             if constexpr (!TAN) {
-                const double lam = double(a.lam[v]), mu = double(a.mu[v]);
+                T tl, tm;
+                material_at(m, (unsigned)v, tl, tm);
+                const double lam = double(tl), mu = double(tm);
                 #pragma unroll
                 for (int k = 0; k < s.np; ++k) {
                     const Grad<DIM> f = add<DIM>(point_grad<DIM, double>(s, s.ni + k, u, sc), Fb);
@@ -650,9 +682,9 @@ __global__ __launch_bounds__(NT) void k_small_finite(SmallArgs<T> a) {
         __syncthreads();
         bool done = false;
         for (int it = 0; it < a.max_newton; ++it) {
-            const double nP = sqrt(all_sum(apply(std::false_type{}), m.red));
+            const double nP = sqrt(all_sum(apply(std::false_type{}), m.red, turn));
             forward<T>(a, m.W, m.tw, m.pass);
-            double rho = residual_step<false>(a, m, T(0));
+            double rho = residual_step<false>(a, m, T(0), turn);
             const double nG = sqrt(rho / a.w);
             rel_eq = nP > 0.0 ? nG / nP : 0.0;
             if (nG <= a.equil_tol * nP) {
@@ -668,11 +700,11 @@ __global__ __launch_bounds__(NT) void k_small_finite(SmallArgs<T> a) {
                 direction<T>(a, m, T(0));
             }
             while (on) {
-                const double pq = all_sum(apply(std::true_type{}), m.red);
+                const double pq = all_sum(apply(std::true_type{}), m.red, turn);
                 if (!(pq > 0.0) || !isfinite(pq)) break;
                 const double alpha = rho / pq;
                 forward<T>(a, m.W, m.tw, m.pass);
-                const double r = residual_step<true>(a, m, T(alpha));
+                const double r = residual_step<true>(a, m, T(alpha), turn);
                 for (int e = threadIdx.x; e < DIM * a.N; e += NT) m.X[e] += alpha * double(m.P[e]);
                 ++iters;
                 if (!isfinite(r)) break;
@@ -686,7 +718,7 @@ __global__ __launch_bounds__(NT) void k_small_finite(SmallArgs<T> a) {
             __syncthreads();
             double s1 = 0.0, s2 = 0.0;
             for (int v = threadIdx.x; v < a.N; v += NT) {
-                const Place<DIM> pl(a.n, (unsigned)v);
+                const Place<DIM> pl(a.n, (unsigned)v, a.d_last.div((uint32_t)v));
                 double u[32][DIM], d[32][DIM];
                 lds_nodes<double>(s, m.F, a.N, pl, u);
                 lds_nodes<double>(s, m.X, a.N, pl, d);
@@ -703,7 +735,7 @@ __global__ __launch_bounds__(NT) void k_small_finite(SmallArgs<T> a) {
                     }
                 }
             }
-            const double nd = sqrt(all_sum(s1, m.red)), nf = sqrt(all_sum(s2, m.red));
+            const double nd = sqrt(all_sum(s1, m.red, turn)), nf = sqrt(all_sum(s2, m.red, turn));
             for (int e = threadIdx.x; e < DIM * a.N; e += NT) m.F[e] += m.X[e];
             __syncthreads();
             ++newton;
@@ -733,8 +765,9 @@ __global__ __launch_bounds__(NT) void k_small_finite(SmallArgs<T> a) {
 // ---------------------------------------------------------------------------
 struct Shape {
     int S;                  // points of a row of W
-    size_t lds;             // bytes without the table
-    size_t table;
+    size_t lds;             // bytes without what may also stay in global memory
+    size_t table, mat;      // of the inverses, of the material
+    bool table_in, mat_in;  // kept in LDS as well
     bool fits;
 };
 
@@ -746,9 +779,12 @@ Shape shape_of(const feh_plan &p, bool finite) {
     auto up = [](size_t b) { return (b + 15) & ~size_t(15); };
     const size_t points = (size_t)rows * h.S * DIM, values = (size_t)DIM * p.N;
     h.lds = up(values * sizeof(T)) + up(points * sizeof(Cx<T>)) + up((size_t)DIM * p.Nspec * sizeof(Cx<T>)) +
-            up(values * (finite || p.u_f64 ? 8 : sizeof(T))) + up(finite ? values * 8 : 0) + up((NW + 1) * 8);
+            up(values * (finite || p.u_f64 ? 8 : sizeof(T))) + up(finite ? values * 8 : 0) + up(2 * NW * 8);
     for (int x = 0; x < DIM; ++x) h.lds += up((size_t)p.n[x] * sizeof(Cx<T>)) + up(5 * kMaxRadixCount * 4);
     h.table = up(4 * (size_t)p.Nspec * sizeof(T));
+    h.mat = 2 * up((size_t)p.N * sizeof(T));
+    h.mat_in = h.lds + h.mat <= kLdsUse;
+    h.table_in = h.lds + (h.mat_in ? h.mat : 0) + h.table <= kLdsUse;
     h.fits = h.lds <= kLdsUse && points <= (size_t)kPoints<T> * NT;
     if (!h.fits) return h;
     for (int x = 0; x < DIM; ++x) {
@@ -806,7 +842,8 @@ SmallArgs<T> small_args(const feh_plan &p, const Shape &h) {
     a.Ebar = p.ptr<const double>(p.off_ebar);
     a.vol = T(0.5);
     a.invN = 1.0 / (double)p.N;
-    a.table_lds = h.lds + h.table <= kLdsUse ? 1 : 0;
+    a.table_lds = h.table_in ? 1 : 0;
+    a.mat_lds = h.mat_in ? 1 : 0;
     return a;
 }
 
@@ -820,7 +857,7 @@ int solve_t(const feh_plan &p, double tol, int max_iter) {
     a.max_iter = max_iter;
     CK(launch_inverse_table(p));
     auto run = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(p.L), dim3(NT), h.lds + (a.table_lds ? h.table : 0), p.stream, a);
+        hipLaunchKernelGGL(kernel, dim3(p.L), dim3(NT), h.lds + (h.table_in ? h.table : 0) + (h.mat_in ? h.mat : 0), p.stream, a);
     };
     if (p.u_f64) run(k_small_solve<T, double>);
     else run(k_small_solve<T, T>);
@@ -844,7 +881,7 @@ int finite_t(const feh_plan &p, int kind, const SmallFinite &f) {
     a.equil_tol = f.equil_tol;
     CK(launch_inverse_table(p));
     auto run = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(p.L), dim3(NT), h.lds + (a.table_lds ? h.table : 0), p.stream, a);
+        hipLaunchKernelGGL(kernel, dim3(p.L), dim3(NT), h.lds + (h.table_in ? h.table : 0) + (h.mat_in ? h.mat : 0), p.stream, a);
     };
     switch (kind) {
     case FEH_DERIV_FE: run(k_small_finite<T, FEH_DERIV_FE>); break;

@@ -33,6 +33,8 @@
 // which the hardware drops, so the node phase has no branch.  The fused CG
 // variant accumulates p.q in FP64 for the step length (the update of p and u
 // is fused into the last inverse FFT pass).
+#include <algorithm>
+
 #include "device_common.hpp"
 
 namespace feh {
@@ -603,12 +605,23 @@ __global__ __launch_bounds__((Tile<DIM, VYT>::NT)) void k_stencil(SK<T> a) {
     }
 }
 
-// Planes per workgroup march: 32 in 3D; 8 in 2D, whose grids are small enough
-// that the march length (not HBM) bounds a launch once most load cases of a
-// batch have converged.
-int xchunk(int n0, int dim) {
-    const int c = dim == 3 ? 32 : 8;
-    return n0 < c ? n0 : c;
+// Planes per workgroup march: 32 in 3D and 8 in 2D (whose rows are short of
+// HBM work), where that leaves four workgroups for every CU; a march evaluates
+// one plane more than it updates.  With fewer the launch lasts as long as one
+// march, and halving it (down to 4 and 2 planes) is the faster: FP32 64^3 x 6
+// load cases 46 -> 33 us, 32^3 x 6 38 -> 13, FP64 256^2 x 3 11.7 -> 10.3; at
+// 128^3 x 6, which fills the chip, 16 planes are even with 32 and 8 slower
+// (163, 163, 173 us).  Counted with 8-row tiles whatever the tile height, and
+// no further than the plan's partial sums have room (part_stride; 0 while the
+// plan is laid out).
+int xchunk(const feh_plan &p) {
+    const long long n0 = p.n[0];
+    const long long tiles = p.dim == 3 ? ((p.n[1] + 6) / 7) * ((p.n[2] + 30) / 31) : (p.n[1] + 254) / 255;
+    int c = p.dim == 3 ? 32 : 8;
+    const int least = p.dim == 3 ? 4 : 2;
+    while (c > least && (n0 + c - 1) / c * tiles * p.L < 1024 && (n0 + c / 2 - 1) / (c / 2) * tiles <= (long long)p.part_stride)
+        c /= 2;
+    return (int)std::min<long long>(n0, c);
 }
 
 template <typename T, int DIM, int VYT>
@@ -646,7 +659,7 @@ int launch_t(const feh_plan &p, int mode, const StencilArgs &sa) {
     if ((long long)a.n1 * a.n2 * (long long)sizeof(T) >= (1LL << 31))
         return set_error(FEH_EINVAL, "stencil: one plane of a field must stay below 2 GiB");
     a.N = p.N;
-    a.xc = xchunk(a.n0, DIM);
+    a.xc = xchunk(p);
     a.nchunk = (a.n0 + a.xc - 1) / a.xc;
     a.nty = (a.n1 + TL::SY - 1) / TL::SY;
     a.ntz = (a.n2 + TL::SZ - 1) / TL::SZ;
@@ -680,7 +693,7 @@ int stencil_rows(const feh_plan &p) {
 
 int stencil_num_parts(const feh_plan &p) {
     const int n0 = (int)p.n[0];
-    const int xc = xchunk(n0, p.dim);
+    const int xc = xchunk(p);
     const int nchunk = (n0 + xc - 1) / xc;
     if (p.dim == 3) {
         const int sy = stencil_rows(p) - 1, sz = 31;

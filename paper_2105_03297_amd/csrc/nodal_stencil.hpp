@@ -209,11 +209,11 @@ __device__ __forceinline__ void tangent_column(const Grad<DIM> &f, const Grad<DI
 template <int DIM>
 struct Place {
     unsigned o[3][5];  // wrapped axis offsets at -2 .. 2, scaled by the axis stride
-    __device__ __forceinline__ Place(const int (&n)[3], unsigned v) {
+    __device__ __forceinline__ Place(const int (&n)[3], unsigned v) : Place(n, v, v / (unsigned)n[DIM - 1]) {}
+    // with the row v / n_last
+    __device__ __forceinline__ Place(const int (&n)[3], unsigned v, unsigned r) {
         int c[3] = {0, 0, 0};
-        const unsigned last = (unsigned)n[DIM - 1];
-        const unsigned r = v / last;
-        c[DIM - 1] = (int)(v - r * last);
+        c[DIM - 1] = (int)(v - r * (unsigned)n[DIM - 1]);
         if constexpr (DIM == 3) {
             c[0] = (int)(r / (unsigned)n[1]);
             c[1] = (int)(r - (unsigned)c[0] * (unsigned)n[1]);

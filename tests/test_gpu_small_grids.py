@@ -37,8 +37,8 @@ def test_one_workgroup_solve(shape, prec):
     hz.close()
     for x, y, t in ((a, b, tol), (cap, capb, 1e-12 if prec == "fp64" else 1e-5)):
         for p, q in zip(x["report"], y["report"]):
-            if max(p["rel_residual"], q["rel_residual"]) < 1e-6 * t:
-                continue  # solved to the last bit or to zero: the cap at tol 0 may or may not be what ended it
+            if max(p["rel_residual"], q["rel_residual"]) < 1e3 * (2.0 ** -53 if prec == "fp64" else 2.0 ** -24):
+                continue  # at rounding: solved to the last bit or to zero: the cap at tol 0 may or may not be what ended it
             assert p["status"] == q["status"] and abs(p["iterations"] - q["iterations"]) <= 1
         un = float(y["u"].abs().max())
         assert float((x["u"] - y["u"]).abs().max()) <= 10 * t * un
