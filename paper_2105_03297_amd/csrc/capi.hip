@@ -396,14 +396,22 @@ int cg_iteration(const feh_plan &p, LcState *st, double tol, int max_iter) {
     sa.partial = part;
     sa.state = st;
     sa.unit_volume = true;
+    const bool march = p.op && nodal_marches(p, p.op->kind);
     {
         ProfScope ps(p, 0);
-        if (p.op) CK(launch_nodal_tangent(p, *p.op, sa.in0, sa.out0, st));
-        else CK(launch_stencil(p, ST_CG, sa));
+        if (march) {
+            sa.u = p.op->u;
+            sa.Ebar = p.op->Fbar;
+            CK(launch_stencil(p, ST_TANGENT, sa));
+        } else if (p.op) {
+            CK(launch_nodal_tangent(p, *p.op, sa.in0, sa.out0, st));
+        } else {
+            CK(launch_stencil(p, ST_CG, sa));
+        }
     }
     {
         ProfScope ps(p, 1);
-        CK(launch_finish_pq(p, st, part, p.op ? nodal_num_parts(p) : stencil_num_parts(p)));
+        CK(launch_finish_pq(p, st, part, p.op && !march ? nodal_num_parts(p) : stencil_num_parts(p)));
     }
     FftArgs fa;
     fa.r = p.ws + p.off_r;

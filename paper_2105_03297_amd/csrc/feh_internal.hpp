@@ -216,13 +216,15 @@ enum StencilMode {
     ST_APPLY = 0,   // q = K p
     ST_CG = 1,      // p_new = z + beta p_old (or z), q = K p_new, u += alpha_pend p_old, partial p.q
     ST_RESID = 2,   // r = -B^T C (Ebar + B u)   (u may be null: right-hand side)
-    ST_DIV = 3      // q = B^T C e for the element field e (projection test export)
+    ST_DIV = 3,     // q = B^T C e for the element field e (projection test export)
+    ST_TANGENT = 4  // 3D: q = B^T (K(F) : B p), F = Fbar (Ebar) + B u, finite strain; partial p.q
 };
 
 struct StencilArgs {
     const void *in0 = nullptr;   // p (APPLY, CG), u (RESID, nullable)
     void *out0 = nullptr;        // q (APPLY, CG), r (RESID)
-    const double *Ebar = nullptr;// device [L][D][D] (RESID)
+    const double *Ebar = nullptr;// device [L][D][D] (RESID; TANGENT: Fbar)
+    const double *u = nullptr;   // TANGENT: displacement fluctuation [L][D][N]
     double *partial = nullptr;   // [L][part_stride] (CG)
     const LcState *state = nullptr;
     bool identity_material = false;  // lambda = 0, mu = 1/2 (preconditioner tests)
@@ -344,6 +346,7 @@ struct NodalOp {
     double *partial = nullptr;
 };
 bool nodal_kind(int kind, int dim);
+bool nodal_marches(const feh_plan &p, int kind);  // the tangent runs as ST_TANGENT of kern_stencil.hip
 int nodal_num_parts(const feh_plan &p);
 int launch_nodal_tangent(const feh_plan &p, const NodalOp &op, const void *pv, void *q, const LcState *st);  // p.q
 int launch_nodal_residual(const feh_plan &p, const NodalOp &op, void *r);  // |P|^2 over the points

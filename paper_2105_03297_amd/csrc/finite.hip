@@ -408,7 +408,7 @@ struct NLayout {
 NLayout make_nlayout(const feh_plan &p) {
     NLayout n{};
     n.cg = nodal_layout(p);
-    n.part_stride = (size_t)std::max(nodal_num_parts(p), first_num_parts(p));
+    n.part_stride = (size_t)std::max({nodal_num_parts(p), first_num_parts(p), stencil_num_parts(p)});
     size_t o = n.cg.total;
     auto take = [&](size_t b) {
         const size_t at = o;

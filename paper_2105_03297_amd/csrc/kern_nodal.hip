@@ -24,7 +24,8 @@
 // a late Newton step diverged on it.)  That needs a point's column to be the
 // same number for every node that forms it: products and sums are written as
 // fma or kept apart (no contraction), never left to the compiler.
-// Bound: FP64 arithmetic in 3D (about 2000 operations a node for the tangent).
+// Bound: FP64 arithmetic in 3D (about 2000 operations a node for the tangent,
+// which larger 3D FE grids evaluate once a tetrahedron: nodal_marches()).
 #include <algorithm>
 
 #include "nodal_stencil.hpp"
@@ -303,6 +304,19 @@ int dispatch(const feh_plan &p, const NK<T> &a, int kind, int what) {
 
 bool nodal_kind(int kind, int dim) {
     return kind == FEH_DERIV_FE || kind == FEH_DERIV_FD || kind == FEH_DERIV_CD || (kind == FEH_DERIV_LS && dim == 2);
+}
+
+// 3D linear elements: the tangent marches with the edge fluxes exchanged
+// through LDS, so that each tetrahedron is evaluated once (and a third again
+// on the tiles' borders) where the gather evaluates it for each of its four
+// nodes, with 512 registers and so one wave per SIMD besides.  FP32 128^3, one
+// load case: 341 -> 132 us.  A march is a chain of planes, though: while every
+// node has its own lane on the chip at once (256 CUs x 4 SIMDs x one wave) the
+// gather is the faster (whole solves, gather and march: 32^3 2.48 and 2.75 ms,
+// 4 x 60 x 200 2.64 and 2.75; beyond it 48^3 3.31 and 3.04, 32^3 x 6 load
+// cases 3.94 and 3.60).
+bool nodal_marches(const feh_plan &p, int kind) {
+    return p.dim == 3 && kind == FEH_DERIV_FE && stencil_rows(p) == 8 && (long long)p.N * p.L > 256 * 4 * 64;
 }
 
 int nodal_num_parts(const feh_plan &p) {

@@ -872,7 +872,7 @@ static int post_t(const feh_plan &p, const void *u, const double *Ebar, void *st
     if (march_ok(p)) {
         MarchGeom geo = p.dim == 3 ? march_geom<3>(p) : march_geom<2>(p);
         // shorter marches while the chip is part empty and the partial sums
-        // have room (32^2 x 3 load cases: 35 -> POST_FIGURE us)
+        // have room (32^2 x 3 load cases: 35 -> 19 us)
         const int room = post_num_parts(p), n0 = (int)p.n[0];
         while (geo.chunk > 2 && (long long)geo.nty * geo.ntz * geo.nchunk * p.L < 1024) {
             const int c = geo.chunk / 2, k = (n0 + c - 1) / c;

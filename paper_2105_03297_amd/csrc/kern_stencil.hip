@@ -34,6 +34,7 @@
 // variant accumulates p.q in FP64 for the step length (the update of p and u
 // is fused into the last inverse FFT pass).
 #include <algorithm>
+#include <type_traits>
 
 #include "device_common.hpp"
 
@@ -127,6 +128,80 @@ __device__ __forceinline__ void voxel3(const T (&P)[8][3], T lam, T mu, const T 
     tet_from_nodes<T, 2, 1, 0, UNIT, EB>(P, lam, mu, ih, Eb, E);
 }
 
+// Finite strain (Saint Venant-Kirchhoff): edge fluxes of dP = X S + F dS of one
+// tetrahedron with axis path (A0, A1, A2), F = Fbar + grad u, X = grad p,
+// S = lam tr(E) I + 2 mu E, E = (F^T F - I) / 2, dS = lam tr(dE) I + 2 mu dE,
+// dE = sym(F^T X), in FP64; Fb[a][i] = Fbar_ia.
+// The corner values are read for each tetrahedron anew, by u(c, i) and p(c, i):
+// kept for all six, the edge differences alone take 144 registers.
+template <int A0, int A1, int A2, bool UNIT, typename FU, typename FP>
+__device__ __forceinline__ void tet_tangent(const FU &u, const FP &p, double lam, double mu,
+                                            const double (&ih)[3], const double (&Fb)[3][3], double (&E)[36]) {
+    asm volatile("" ::: "memory");
+    constexpr int V1 = 1 << A0, V2 = V1 | (1 << A1);
+    constexpr int k[3] = {EdgeK<A0, 0>::k, EdgeK<A1, V1>::k, EdgeK<A2, V2>::k};
+    constexpr int A[3] = {A0, A1, A2}, V[4] = {0, V1, V2, 7};
+    double f[3][3], x[3][3];  // columns, by axis
+    #pragma unroll
+    for (int e = 0; e < 3; ++e)
+        #pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            const double du = u(V[e + 1], i) - u(V[e], i), dp = p(V[e + 1], i) - p(V[e], i);
+            f[A[e]][i] = UNIT ? du + Fb[A[e]][i] : fma(du, ih[A[e]], Fb[A[e]][i]);
+            x[A[e]][i] = UNIT ? dp : dp * ih[A[e]];
+        }
+    auto dot = [](const double (&a)[3], const double (&b)[3]) { return fma(a[2], b[2], fma(a[1], b[1], a[0] * b[0])); };
+    double s[3][3], d[3][3];
+    double tr = -3.0, trx = 0.0;
+    #pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const double ff = dot(f[a], f[a]), fx = dot(f[a], x[a]);
+        tr += ff;
+        trx += fx;
+        s[a][a] = mu * (ff - 1.0);
+        d[a][a] = 2.0 * mu * fx;
+    }
+    #pragma unroll
+    for (int a = 0; a < 3; ++a)
+        #pragma unroll
+        for (int b = a + 1; b < 3; ++b) {
+            s[a][b] = s[b][a] = mu * dot(f[a], f[b]);
+            d[a][b] = d[b][a] = mu * (dot(f[a], x[b]) + dot(x[a], f[b]));
+        }
+    #pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        s[a][a] = fma(0.5 * lam, tr, s[a][a]);
+        d[a][a] = fma(lam, trx, d[a][a]);
+    }
+    #pragma unroll
+    for (int e = 0; e < 3; ++e)
+        #pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            const int a = A[e];
+            double c = x[0][i] * s[0][a];
+            c = fma(f[0][i], d[0][a], c);
+            #pragma unroll
+            for (int j = 1; j < 3; ++j) {
+                c = fma(x[j][i], s[j][a], c);
+                c = fma(f[j][i], d[j][a], c);
+            }
+            E[(a * 4 + k[e]) * 3 + i] += UNIT ? c : c * ih[a];
+        }
+}
+
+template <bool UNIT, typename FU, typename FP>
+__device__ __forceinline__ void voxel3_tangent(const FU &u, const FP &p, double lam, double mu, const double (&ih)[3],
+                                               const double (&Fb)[3][3], double (&E)[36]) {
+    #pragma unroll
+    for (int j = 0; j < 36; ++j) E[j] = -0.0;
+    tet_tangent<0, 1, 2, UNIT>(u, p, lam, mu, ih, Fb, E);
+    tet_tangent<0, 2, 1, UNIT>(u, p, lam, mu, ih, Fb, E);
+    tet_tangent<1, 0, 2, UNIT>(u, p, lam, mu, ih, Fb, E);
+    tet_tangent<1, 2, 0, UNIT>(u, p, lam, mu, ih, Fb, E);
+    tet_tangent<2, 0, 1, UNIT>(u, p, lam, mu, ih, Fb, E);
+    tet_tangent<2, 1, 0, UNIT>(u, p, lam, mu, ih, Fb, E);
+}
+
 // Element field given directly (projection test export): fluxes of |e| sym(e_T).
 template <typename T, int A0, int A1, int A2>
 __device__ __forceinline__ void tet_div(const T *e, T vol, const T (&ih)[3], T (&E)[36]) {
@@ -195,6 +270,8 @@ struct SK {
     int part_stride;
     T ih[3];
     T vol;
+    const double *u;   // ST_TANGENT: displacement fluctuation
+    double ihd[3], vold;
     int ident;         // lambda = 0, mu = 1/2 everywhere
     int G;             // load cases per microstructure (material of load case l: l / G)
 };
@@ -233,8 +310,16 @@ __device__ __forceinline__ double from_left(double v) {
     return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
 }
 
+// TAN (ST_TANGENT, 3D): the finite-strain tangent with the same march, in FP64.
+// It keeps u and p of both node planes of a voxel plane in LDS (70 KB, two
+// workgroups a CU) and reads them anew for each tetrahedron: with the corners
+// in registers as the linear operator has them, 255 registers spilled at two
+// waves per SIMD; so none do.  Bound: FP64 arithmetic (128^3: 132 us, of which
+// the products and sums are about 60).
 template <typename T, int DIM, int MODE, bool UNIT, int VYT>
-__global__ __launch_bounds__((Tile<DIM, VYT>::NT)) void k_stencil(SK<T> a) {
+__global__ __launch_bounds__((Tile<DIM, VYT>::NT)) __attribute__((amdgpu_waves_per_eu(MODE == ST_TANGENT ? 2 : 1))) void k_stencil(SK<T> a) {
+    constexpr bool TAN = MODE == ST_TANGENT;
+    using CT = std::conditional_t<TAN, double, T>;  // of the fluxes and forces
     using TL = Tile<DIM, VYT>;
     constexpr int VY = TL::VY, VZ = TL::VZ, HY = TL::HY, NC = TL::NC, NEDGE = TL::NEDGE;
     constexpr int EY = VY + HY, EZ = VZ + 1;     // node plane of the tile
@@ -243,11 +328,13 @@ __global__ __launch_bounds__((Tile<DIM, VYT>::NT)) void k_stencil(SK<T> a) {
     constexpr int NSE = (NE + NT - 1) / NT;      // node-plane slots per thread
     static_assert(VY * VZ == NT, "one voxel per thread");
     static_assert(DIM == 2 || VZ == 32, "3D: one row of voxels per half wavefront");
-    __shared__ T Pl[NC][NE];                     // one node plane
+    constexpr int NPL = TAN ? 2 : 1;
+    __shared__ T Pl[NPL][NC][NE];                // one node plane (TAN: two, in turn)
     // edge fluxes passed through LDS, one column per voxel: in 3D only the 24
     // values the next row of voxels needs (the left neighbour's come by DPP)
     constexpr int NX = DIM == 3 ? 24 : NQ;
-    __shared__ T Es[NX][NT];
+    __shared__ CT Es[NX][NT];
+    __shared__ double Ul[NPL][TAN ? NC : 1][TAN ? NE : 1];  // TAN: the displacement's planes
     __shared__ double red[NT / 64];
 
     const int tid = threadIdx.x;
@@ -261,8 +348,15 @@ __global__ __launch_bounds__((Tile<DIM, VYT>::NT)) void k_stencil(SK<T> a) {
     const int blk_in_lc = (ch * a.nty + ty_t) * a.ntz + tz_t;
 
     // load cases that have stopped iterating
-    if constexpr (MODE == ST_CG) {
+    if constexpr (MODE == ST_CG || TAN) {
         if (!a.st[lc].active) return;
+    }
+    double Fb[3][3] = {};
+    if constexpr (TAN) {
+        #pragma unroll
+        for (int i = 0; i < 3; ++i)
+            #pragma unroll
+            for (int j = 0; j < 3; ++j) Fb[j][i] = a.Ebar[lc * 9 + 3 * i + j];
     }
     T Eb[6] = {T(0), T(0), T(0), T(0), T(0), T(0)};
     if constexpr (MODE == ST_RESID) {
@@ -337,6 +431,7 @@ __global__ __launch_bounds__((Tile<DIM, VYT>::NT)) void k_stencil(SK<T> a) {
     // plane.  Every load is unconditional (unused slots and planes past the
     // chunk re-read valid addresses).
     T rz[NSE][NC];
+    double ru[TAN ? NSE : 1][NC];
     T mlam = T(0), mmu = T(0);
     auto fetch_nodes = [&](int P) __attribute__((always_inline)) {
         const long long base = lcoff + (long long)wrap(P, a.n0) * plane;
@@ -344,7 +439,9 @@ __global__ __launch_bounds__((Tile<DIM, VYT>::NT)) void k_stencil(SK<T> a) {
         for (int s = 0; s < NSE; ++s) {
             #pragma unroll
             for (int c = 0; c < NC; ++c) {
-                if constexpr (MODE == ST_APPLY || MODE == ST_CG) {
+                if constexpr (TAN)
+                    ru[s][c] = buffer_ld<double>(raw_buffer(a.u + base + c * N, plane * 8), e_boff[s] * (unsigned)(8 / sizeof(T)));
+                if constexpr (MODE == ST_APPLY || MODE == ST_CG || TAN) {
                     rz[s][c] = buffer_ld<T>(raw_buffer(a.in0 + base + c * N, plane_bytes), e_boff[s]);
                 } else if constexpr (MODE == ST_RESID) {
                     rz[s][c] = a.in0 ? buffer_ld<T>(raw_buffer(a.in0 + base + c * N, plane_bytes), e_boff[s]) : T(0);
@@ -355,13 +452,14 @@ __global__ __launch_bounds__((Tile<DIM, VYT>::NT)) void k_stencil(SK<T> a) {
     // stage the fetched node plane in LDS (one plane only: the previous plane's corners
     // stay in registers); returns the thread's own node value in own[]
     T own[NC];
-    auto commit_nodes = [&]() __attribute__((always_inline)) {
+    auto commit_nodes = [&](int w) __attribute__((always_inline)) {
         #pragma unroll
         for (int s = 0; s < NSE; ++s) {
             #pragma unroll
             for (int c = 0; c < NC; ++c) {
-                Pl[c][e_lds[s]] = rz[s][c];
+                Pl[w][c][e_lds[s]] = rz[s][c];
                 if (s == 0) own[c] = rz[s][c];
+                if constexpr (TAN) Ul[w][c][e_lds[s]] = ru[s][c];
             }
         }
     };
@@ -381,23 +479,25 @@ __global__ __launch_bounds__((Tile<DIM, VYT>::NT)) void k_stencil(SK<T> a) {
     // the differences of the other axes' edges whose voxels lie in the
     // previous plane
     constexpr int NXE = DIM == 3 ? 4 : 2;  // axis-0 edges per voxel
-    T cx[NXE * NC];
-    T cq[NC];
+    CT cx[NXE * NC];
+    CT cq[NC];
     #pragma unroll
-    for (int j = 0; j < NXE * NC; ++j) cx[j] = T(0);
+    for (int j = 0; j < NXE * NC; ++j) cx[j] = CT(0);
     #pragma unroll
-    for (int c = 0; c < NC; ++c) cq[c] = T(0);
+    for (int c = 0; c < NC; ++c) cq[c] = CT(0);
     double acc = 0.0;
 
     if constexpr (MODE != ST_DIV) {
         fetch_nodes(x0 - 1);
-        commit_nodes();
+        commit_nodes(0);
         fetch_nodes(x0);
         __syncthreads();
         #pragma unroll
         for (int k = 0; k < NK; ++k) {
             #pragma unroll
-            for (int c = 0; c < NC; ++c) Pc[k][c] = (k == 0) ? own[c] : Pl[c][corner_lds(k)];
+            for (int c = 0; c < NC; ++c) {
+                Pc[k][c] = (k == 0) ? own[c] : Pl[0][c][corner_lds(k)];
+            }
         }
         __syncthreads();
     }
@@ -410,23 +510,24 @@ __global__ __launch_bounds__((Tile<DIM, VYT>::NT)) void k_stencil(SK<T> a) {
 
     // one step of the march: the voxels of plane X, then the nodes of plane X
     // (the first step, plane x0 - 1, only primes the carried terms)
-    auto step = [&](const int X, auto first) __attribute__((always_inline)) {
+    auto step = [&](const int X, auto first, auto buf) __attribute__((always_inline)) {
         constexpr bool FIRST = decltype(first)::value;
+        constexpr int W = TAN ? decltype(buf)::value : 0;  // the LDS plane that takes X + 1
         // ---- stage plane X+1, prefetch plane X+2 and the material of voxel plane X+1
-        if constexpr (MODE != ST_DIV) commit_nodes();
+        if constexpr (MODE != ST_DIV) commit_nodes(W);
         const T clam = mlam, cmu = mmu;
         if constexpr (MODE != ST_DIV) fetch_nodes(min(X + 2, x1));
         fetch_material(min(X + 1, x1 - 1));
         __syncthreads();
         // ---- voxel phase: the thread's voxel in plane X
         T pown[NC];  // p at the thread's own node of plane X
-        T q[NC], nq[NC];
+        CT q[NC], nq[NC];
         #pragma unroll
         for (int i = 0; i < NC; ++i) {
             q[i] = cq[i];
-            nq[i] = T(-0.0);  // x + (-0) = x: the first term folds into a move
+            nq[i] = CT(-0.0);  // x + (-0) = x: the first term folds into a move
         }
-        T oy[12];    // 3D: the own voxel's axis-1 edge fluxes, kept for the node phase
+        CT oy[12];   // 3D: the own voxel's axis-1 edge fluxes, kept for the node phase
         {
             T lam, mu;
             if (a.ident) {
@@ -437,8 +538,17 @@ __global__ __launch_bounds__((Tile<DIM, VYT>::NT)) void k_stencil(SK<T> a) {
                 mu = cmu * a.vol;
             }
             if constexpr (DIM == 3) {
-                T E[36];
-                if constexpr (MODE == ST_DIV) {
+                CT E[36];
+                if constexpr (TAN) {
+                    #pragma unroll
+                    for (int i = 0; i < 3; ++i) {
+                        pown[i] = Pc[0][i];
+                        Pc[0][i] = own[i];
+                    }
+                    auto u = [&](int c, int i) { return Ul[(c & 1) ? W : 1 - W][i][corner_lds(c >> 1)]; };
+                    auto pv = [&](int c, int i) { return double(Pl[(c & 1) ? W : 1 - W][i][corner_lds(c >> 1)]); };
+                    voxel3_tangent<UNIT>(u, pv, double(clam) * a.vold, double(cmu) * a.vold, a.ihd, Fb, E);
+                } else if constexpr (MODE == ST_DIV) {
                     const long long vidx = (long long)wrap(X, a.n0) * plane + v_off;
                     const T *e = a.in0 + ((long long)lc * N + vidx) * 54;
                     #pragma unroll
@@ -457,7 +567,7 @@ __global__ __launch_bounds__((Tile<DIM, VYT>::NT)) void k_stencil(SK<T> a) {
                         #pragma unroll
                         for (int i = 0; i < 3; ++i) {
                             P[2 * k][i] = Pc[k][i];
-                            P[2 * k + 1][i] = (k == 0) ? own[i] : Pl[i][corner_lds(k)];
+                            P[2 * k + 1][i] = (k == 0) ? own[i] : Pl[0][i][corner_lds(k)];
                         }
                     }
                     voxel3<T, UNIT, MODE == ST_RESID>(P, lam, mu, a.ih, Eb, E);
@@ -480,11 +590,11 @@ __global__ __launch_bounds__((Tile<DIM, VYT>::NT)) void k_stencil(SK<T> a) {
                 // the latter formed by lane - 1, which holds that voxel
                 #pragma unroll
                 for (int i = 0; i < 3; ++i) {
-                    const T c0 = E[0 + i];
+                    const CT c0 = E[0 + i];
                     q[i] += cx[0 * 3 + i] - c0;
                     cx[0 * 3 + i] = c0;
-                    const T c2 = E[6 + i];
-                    const T d2 = cx[2 * 3 + i] - c2;
+                    const CT c2 = E[6 + i];
+                    const CT d2 = cx[2 * 3 + i] - c2;
                     cx[2 * 3 + i] = c2;
                     q[i] += from_left(d2);
                     q[i] += from_left(E[24 + i]) - E[24 + i];
@@ -503,7 +613,7 @@ __global__ __launch_bounds__((Tile<DIM, VYT>::NT)) void k_stencil(SK<T> a) {
                         #pragma unroll
                         for (int i = 0; i < 2; ++i) {
                             P[2 * k][i] = Pc[k][i];
-                            P[2 * k + 1][i] = (k == 0) ? own[i] : Pl[i][corner_lds(k)];
+                            P[2 * k + 1][i] = (k == 0) ? own[i] : Pl[0][i][corner_lds(k)];
                         }
                     }
                     const T Eb2[3] = {Eb[0], Eb[1], Eb[2]};
@@ -528,17 +638,17 @@ __global__ __launch_bounds__((Tile<DIM, VYT>::NT)) void k_stencil(SK<T> a) {
                 // fluxes of the voxel above (row ty - 1); row 0 reads its own
                 // column (it updates no node and feeds no neighbour that does)
                 const int ia = ty >= 1 ? tid - VZ : tid;
-                T A[24];
+                CT A[24];
                 #pragma unroll
                 for (int j = 0; j < 24; ++j) A[j] = Es[j][ia];
                 #pragma unroll
                 for (int i = 0; i < 3; ++i) {
                     // x-edges c = (0,1,0) (voxel above) and c = (0,1,1) (above-left, from lane - 1)
-                    const T c1 = A[0 + i];
+                    const CT c1 = A[0 + i];
                     q[i] += cx[1 * 3 + i] - c1;
                     cx[1 * 3 + i] = c1;
-                    const T c3 = A[3 + i];
-                    const T d3 = cx[3 * 3 + i] - c3;
+                    const CT c3 = A[3 + i];
+                    const CT d3 = cx[3 * 3 + i] - c3;
                     cx[3 * 3 + i] = c3;
                     q[i] += from_left(d3);
                     // y-edges: above - own (k = 0, 1); above-left - left (k = 2, 3) from lane - 1
@@ -574,10 +684,10 @@ __global__ __launch_bounds__((Tile<DIM, VYT>::NT)) void k_stencil(SK<T> a) {
                 #pragma unroll
                 for (int i = 0; i < NC; ++i) {
                     buffer_st<T>(raw_buffer(a.out0 + lcoff + i * N + (long long)X * plane, plane_bytes), st_boff,
-                                 MODE == ST_RESID ? -q[i] : q[i]);
+                                 MODE == ST_RESID ? T(-q[i]) : T(q[i]));
                     // p.q of every lane (finite values); the lanes that own no
                     // node drop their sum at the end
-                    if constexpr (MODE == ST_CG) acc += double(pown[i]) * double(q[i]);
+                    if constexpr (MODE == ST_CG || TAN) acc += double(pown[i]) * double(T(q[i]));
                 }
             }
             #pragma unroll
@@ -591,14 +701,16 @@ __global__ __launch_bounds__((Tile<DIM, VYT>::NT)) void k_stencil(SK<T> a) {
     };
     // two steps per trip, so that the values carried from one step to the
     // next alternate between two register sets instead of being copied
-    step(x0 - 1, std::true_type{});
+    using B0 = std::integral_constant<int, 0>;
+    using B1 = std::integral_constant<int, 1>;
+    step(x0 - 1, std::true_type{}, B1{});
     for (int X = x0;; X += 2) {
-        step(X, std::false_type{});
+        step(X, std::false_type{}, B0{});
         if (X + 1 >= x1) break;
-        step(X + 1, std::false_type{});
+        step(X + 1, std::false_type{}, B1{});
         if (X + 2 >= x1) break;
     }
-    if constexpr (MODE == ST_CG) {
+    if constexpr (MODE == ST_CG || TAN) {
         if (!owner) acc = 0.0;
         const double s = block_sum<NT>(acc, red);
         if (tid == 0) a.partial[(long long)lc * a.part_stride + blk_in_lc] = s;
@@ -637,6 +749,9 @@ int launch_t(const feh_plan &p, int mode, const StencilArgs &sa) {
     a.st = sa.state;
     a.ident = sa.identity_material ? 1 : 0;
     a.G = p.G;
+    a.u = sa.u;
+    for (int x = 0; x < 3; ++x) a.ihd[x] = 1.0 / p.h[x];
+    a.vold = 1.0 / 6.0;  // ST_TANGENT: the element volume over the voxel's
     if (DIM == 3) {
         a.n0 = (int)p.n[0];
         a.n1 = (int)p.n[1];
@@ -672,6 +787,16 @@ int launch_t(const feh_plan &p, int mode, const StencilArgs &sa) {
         if (unit) hipLaunchKernelGGL((k_stencil<T, DIM, M, true, VYT>), grid, block, 0, p.stream, a);             \
         else hipLaunchKernelGGL((k_stencil<T, DIM, M, false, VYT>), grid, block, 0, p.stream, a);                 \
         break;
+    if (mode == ST_TANGENT) {
+        if constexpr (DIM == 3 && VYT == 8) {
+            if ((long long)a.n1 * a.n2 * 8 >= (1LL << 31))
+                return set_error(FEH_EINVAL, "stencil: one plane of a field must stay below 2 GiB");
+            if (unit) hipLaunchKernelGGL((k_stencil<T, 3, ST_TANGENT, true, 8>), grid, block, 0, p.stream, a);
+            else hipLaunchKernelGGL((k_stencil<T, 3, ST_TANGENT, false, 8>), grid, block, 0, p.stream, a);
+            return hip_check(hipGetLastError(), "tangent launch");
+        }
+        return set_error(FEH_EINVAL, "bad stencil mode");
+    }
     switch (mode) {
         FEH_STENCIL_CASE(ST_APPLY)
         FEH_STENCIL_CASE(ST_CG)
@@ -705,7 +830,7 @@ int stencil_num_parts(const feh_plan &p) {
 int launch_stencil(const feh_plan &p, int mode, const StencilArgs &a) {
     if (p.dim == 2)
         return p.prec == FEH_FP64 ? launch_t<double, 2, 1>(p, mode, a) : launch_t<float, 2, 1>(p, mode, a);
-    if (stencil_rows(p) == 16)
+    if (stencil_rows(p) == 16 && mode != ST_TANGENT)
         return p.prec == FEH_FP64 ? launch_t<double, 3, 16>(p, mode, a) : launch_t<float, 3, 16>(p, mode, a);
     return p.prec == FEH_FP64 ? launch_t<double, 3, 8>(p, mode, a) : launch_t<float, 3, 8>(p, mode, a);
 }

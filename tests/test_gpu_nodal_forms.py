@@ -106,6 +106,40 @@ def test_finite_strain_on_nodal_vectors(kind, shape, prec):
         assert np.abs(got[l] - ref).max() <= (1e-10 if prec == "fp64" else 1e-6)
 
 
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("shape,h,L", [((65, 32, 32), None, 1), ((37, 29, 62), (1.0, 0.5, 2.0), 1), ((33, 9, 225), None, 1),
+                                       ((70, 17, 31), None, 2), ((2, 2, 31), None, 64), ((3, 8, 43), (0.7, 1.3, 0.9), 64)])
+def test_finite_tangent_march_matches_gather(shape, h, L, prec):
+    """3D linear elements above 65 536 nodes times load cases: the tangent as a
+    march, against the gather (which a plan with 16 stencil rows keeps), and
+    grids of the same shape below that number.  Same equations, so Newton's
+    last step, of at most the tolerance, leaves its square and the CG tolerance
+    of that step; both are far below the bounds, which are the rounding of the
+    fields (FP32: 6e-8 of F, a few of them)."""
+    import paper_2105_03297_amd as feh
+    say("finite march", shape, h, L, prec)
+    lam, mu = random_material(shape, seed=29, prec=prec, emax=4.0)
+    rng = np.random.default_rng(7)
+    Fbar = np.array([np.eye(3) * 1.03 + 0.02 * rng.standard_normal((3, 3)) for _ in range(L)])
+    tol = 1e-8 if prec == "fp64" else 1e-4
+    res = []
+    for rows in (8, 16):
+        hz = feh.Homogenizer(shape, n_load=L, precision=prec, h=h)
+        t = feh.feh_plan_tuning(hz.plan)
+        t["stencil_rows"] = rows
+        feh.feh_plan_set_tuning(hz.plan, t)
+        hz.set_material(lam=lam, mu=mu)
+        out = hz.finite_strain_solve(Fbar, kind="fe", newton_tol=tol, equil_tol=0.0,
+                                     cg_tol=1e-3 * tol if prec == "fp64" else tol, fields=True)
+        hz.close()
+        assert all(r["status"] == 0 for r in out["report"])
+        res.append(out)
+    F, G = (o["F"].cpu().numpy().astype(np.float64) for o in res)
+    assert np.abs(F - G).max() <= (1e-10 if prec == "fp64" else 1e-6)
+    for a, b in zip(res[0]["report"], res[1]["report"]):
+        assert a["newton_iterations"] == b["newton_iterations"]
+
+
 def test_plan_solution_survives_finite_strain():
     """The inverse table of the plan is rebuilt for each metric: a small-strain
     solve after a finite-strain one repeats the first bitwise."""
