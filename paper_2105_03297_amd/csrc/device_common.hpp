@@ -74,6 +74,39 @@ __device__ __forceinline__ void buffer_st(__amdgpu_buffer_rsrc_t r, unsigned off
     }
 }
 
+// Orders a wavefront's LDS writes before its later reads and the reads before
+// later writes (the LDS serves a wavefront's accesses in program order, so
+// only the compiler has to be held).
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Writes PER values of each of `run` consecutive records of STRIDE values from
+// LDS, by the `run` lanes of one wavefront that staged a record each: record i
+// at lds + i PER goes to out + i STRIDE.  Consecutive lanes write consecutive
+// values (stored record by record, each store of a wavefront touches a line
+// per lane).
+template <typename T, int PER, int STRIDE>
+__device__ __forceinline__ void store_run(T *out, const T *lds, int lane, int run) {
+    constexpr int B = PER % 9 == 0 ? 9 : 4;  // loads in flight, kept few in registers
+    static_assert(PER % B == 0, "whole groups");
+    wave_lds_fence();
+    #pragma unroll 1
+    for (int k = 0; k < PER; k += B) {
+        T v[B];
+        #pragma unroll
+        for (int i = 0; i < B; ++i) v[i] = lds[lane + (k + i) * run];
+        #pragma unroll
+        for (int i = 0; i < B; ++i) {
+            const unsigned j = (unsigned)(lane + (k + i) * run);
+            out[PER == STRIDE ? j : j + j / PER * (STRIDE - PER)] = v[i];
+        }
+    }
+    wave_lds_fence();
+}
+
 // Deterministic block sum of one double (fixed order), result in thread 0.
 template <int NT>
 __device__ __forceinline__ double block_sum(double v, double *sh) {
