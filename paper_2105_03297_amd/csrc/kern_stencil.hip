@@ -330,9 +330,12 @@ __global__ __launch_bounds__((Tile<DIM, VYT>::NT)) __attribute__((amdgpu_waves_p
     static_assert(DIM == 2 || VZ == 32, "3D: one row of voxels per half wavefront");
     constexpr int NPL = TAN ? 2 : 1;
     __shared__ T Pl[NPL][NC][NE];                // one node plane (TAN: two, in turn)
-    // edge fluxes passed through LDS, one column per voxel: in 3D only the 24
-    // values the next row of voxels needs (the left neighbour's come by DPP)
-    constexpr int NX = DIM == 3 ? 24 : NQ;
+    // edge fluxes passed through LDS, one column per voxel: in 3D only the 18
+    // values the next row of voxels needs (the left neighbour's come by DPP);
+    // with the x- and z-edge fluxes raw (24 values) FP64 128^3 x 6 load cases
+    // took 309 us, now 289, at 600 MB of traffic: bound by the two waves per
+    // SIMD that its 200 registers allow (three, at 168, spill: 290)
+    constexpr int NX = DIM == 3 ? 18 : NQ;
     __shared__ CT Es[NX][NT];
     __shared__ double Ul[NPL][TAN ? NC : 1][TAN ? NE : 1];  // TAN: the displacement's planes
     __shared__ double red[NT / 64];
@@ -580,14 +583,13 @@ __global__ __launch_bounds__((Tile<DIM, VYT>::NT)) __attribute__((amdgpu_waves_p
                         }
                     }
                 }
-                // export the fluxes the row below needs: x1, x3, y0..y3, z2, z3
-                #pragma unroll
-                for (int j = 0; j < 24; ++j) Es[j][tid] = E[j < 6 ? (j < 3 ? 3 + j : 6 + j) : (j < 18 ? 6 + j : 12 + j)];
-                #pragma unroll
-                for (int j = 0; j < 12; ++j) oy[j] = E[12 + j];
                 // terms of the own voxel (x-edge c = 0) and of the left voxel
                 // (x-edge c = (0,0,1), z-edges c = (x,0,0) paired with the own voxel),
-                // the latter formed by lane - 1, which holds that voxel
+                // the latter formed by lane - 1, which holds that voxel; and, for
+                // the node below, the same of the edges one row on (x-edges
+                // c = (0,1,0) and (0,1,1), z-edges c = (x,1,0)), which go to it
+                // together with the raw y-edge fluxes: each difference is formed
+                // of the two fluxes that nearly cancel, here or there
                 #pragma unroll
                 for (int i = 0; i < 3; ++i) {
                     const CT c0 = E[0 + i];
@@ -599,6 +601,21 @@ __global__ __launch_bounds__((Tile<DIM, VYT>::NT)) __attribute__((amdgpu_waves_p
                     q[i] += from_left(d2);
                     q[i] += from_left(E[24 + i]) - E[24 + i];
                     nq[i] += from_left(E[27 + i]) - E[27 + i];
+                    const CT c1 = E[3 + i];
+                    CT below = cx[1 * 3 + i] - c1;
+                    cx[1 * 3 + i] = c1;
+                    const CT c3 = E[9 + i];
+                    const CT d3 = cx[3 * 3 + i] - c3;
+                    cx[3 * 3 + i] = c3;
+                    below += from_left(d3);
+                    below += from_left(E[30 + i]) - E[30 + i];
+                    Es[i][tid] = below;
+                    Es[3 + i][tid] = from_left(E[33 + i]) - E[33 + i];
+                }
+                #pragma unroll
+                for (int j = 0; j < 12; ++j) {
+                    Es[6 + j][tid] = E[12 + j];
+                    oy[j] = E[12 + j];
                 }
             } else {
                 T E[8];
@@ -635,30 +652,21 @@ __global__ __launch_bounds__((Tile<DIM, VYT>::NT)) __attribute__((amdgpu_waves_p
         // ---- node phase (the thread's own node)
         {
             if constexpr (DIM == 3) {
-                // fluxes of the voxel above (row ty - 1); row 0 reads its own
+                // terms of the voxel above (row ty - 1); row 0 reads its own
                 // column (it updates no node and feeds no neighbour that does)
                 const int ia = ty >= 1 ? tid - VZ : tid;
-                CT A[24];
+                CT A[18];
                 #pragma unroll
-                for (int j = 0; j < 24; ++j) A[j] = Es[j][ia];
+                for (int j = 0; j < 18; ++j) A[j] = Es[j][ia];
                 #pragma unroll
                 for (int i = 0; i < 3; ++i) {
-                    // x-edges c = (0,1,0) (voxel above) and c = (0,1,1) (above-left, from lane - 1)
-                    const CT c1 = A[0 + i];
-                    q[i] += cx[1 * 3 + i] - c1;
-                    cx[1 * 3 + i] = c1;
-                    const CT c3 = A[3 + i];
-                    const CT d3 = cx[3 * 3 + i] - c3;
-                    cx[3 * 3 + i] = c3;
-                    q[i] += from_left(d3);
+                    q[i] += A[i];
+                    nq[i] += A[3 + i];
                     // y-edges: above - own (k = 0, 1); above-left - left (k = 2, 3) from lane - 1
                     q[i] += A[6 + i] - oy[0 + i];
                     nq[i] += A[9 + i] - oy[3 + i];
                     q[i] += from_left(A[12 + i] - oy[6 + i]);
                     nq[i] += from_left(A[15 + i] - oy[9 + i]);
-                    // z-edges: above-left (from lane - 1) - above (k = 2, 3)
-                    q[i] += from_left(A[18 + i]) - A[18 + i];
-                    nq[i] += from_left(A[21 + i]) - A[21 + i];
                 }
             } else {
                 // axis-0 edges: c = (0, c1), k = c1
