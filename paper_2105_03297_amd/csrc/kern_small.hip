@@ -8,17 +8,17 @@
 // little it computes; here it is some twenty barriers.  The arithmetic is that
 // of the general path: plan precision for the stencil of the small-strain
 // solve, the transforms and M^-1, FP64 for every sum and for the finite-strain
-// stress; the residual is kept fully transformed (r^ -= alpha q^), which the
-// linear transform allows as the half-transformed one of the general path.
+// stress.
 // Bound: LDS latency and barriers.
 // Measured against the general path (FP64): solve of 3 load cases to 1e-10,
-// 8^2 0.94 -> 0.24 ms, 17^2 1.24 -> 0.47, 32^2 1.70 -> 0.71, 46^2 2.00 -> 1.45;
+// 8^2 0.94 -> 0.24 ms, 17^2 1.24 -> 0.47, 32^2 1.70 -> 0.69, 46^2 2.00 -> 1.45;
 // finite strain, tolerances 1e-10, 17^2 2.9 -> 0.9 ms, 32^2 7.7 -> 3.4.  It is
 // the faster wherever it fits, so the rule is the LDS that a solve needs (up
 // to about 47^2 in FP64, 66^2 in FP32; finite strain 42^2 and 50^2).
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 #include <vector>
 
 #include "fft_butterflies.hpp"
@@ -342,17 +342,17 @@ __device__ __forceinline__ void hooke_column(const Stencil &s, int slot, int c, 
     #pragma unroll
     for (int i = 0; i < DIM; ++i) {
         const T e2 = g(i, c) + g(c, i) + (EB ? T(2) * Eb[i][c] : T(0));  // 2 e_ic
-        col[i] = mu * e2 + (i == c ? lam * tr : T(0));
+        col[i] = i == c ? fma(lam, tr, mu * e2) : mu * e2;
     }
 }
 
-// LDS of a solve: P [D][N], W, R^ (the spectral residual, W's valid points),
+// LDS of a solve: P [D][N], W, R (the residual, [D][N]),
 // X (u, or the increment; in U), [F: the displacement], reduction, material,
 // twiddles, pass lists, table of inverses.  U: the type of X.
 template <typename T, typename U, bool FINITE>
 struct Lds {
-    T *P;
-    Cx<T> *W, *Rh;
+    T *P, *R;
+    Cx<T> *W;
     U *X;
     double *F, *red;
     const T *glam, *gmu;
@@ -370,7 +370,7 @@ struct Lds {
         };
         P = reinterpret_cast<T *>(take(DIM * a.N * (int)sizeof(T)));
         W = reinterpret_cast<Cx<T> *>(take(a.rows * a.S * DIM * (int)sizeof(Cx<T>)));
-        Rh = reinterpret_cast<Cx<T> *>(take(a.nspec * DIM * (int)sizeof(Cx<T>)));
+        R = reinterpret_cast<T *>(take(a.nspec * DIM * (int)sizeof(Cx<T>)));  // at least the N a component
         X = reinterpret_cast<U *>(take(DIM * a.N * (int)sizeof(U)));
         F = reinterpret_cast<double *>(take(FINITE ? DIM * a.N * 8 : 0));
         red = reinterpret_cast<double *>(take(2 * NW * 8));
@@ -424,10 +424,28 @@ __device__ __forceinline__ void material_at(const M &m, unsigned v, T &lam, T &m
     mu = m.in_lds ? m.mu[v] : m.gmu[v];
 }
 
-// STEP false: r^ = spectrum in W; true: r^ -= alpha W.  Then W = z^ = M^-1 r^;
-// returns r.z.
-template <bool STEP, typename T, typename M>
-__device__ __forceinline__ double residual_step(const SmallArgs<T> &a, const M &m, T alpha, int &turn) {
+// r -= alpha q, q in W; r into W for the transform.  The residual is kept as a
+// real field: its rounding is then a real force, which the CG can balance, and
+// the transforms' own enters the preconditioner alone.  (Kept transformed,
+// r^ -= alpha q^, FP32 solves on even grids gathered rounding of 1e-7 of the
+// first residual that no step could take out again: long grids diverged where
+// the general path converges, 900 x 2 at 1e-6.)
+template <typename T, typename M>
+__device__ __forceinline__ void advance(const SmallArgs<T> &a, const M &m, double alpha) {
+    T *w = reinterpret_cast<T *>(m.W);
+    for (int e = threadIdx.x; e < DIM * a.N; e += NT) {
+        const int c = (int)a.d_N.div((uint32_t)e), v = e - c * a.N;
+        const int row = (int)a.d_last.div((uint32_t)v), i = v - row * a.nlast;
+        T &q = w[real_at<T>(a, row, i, c)];
+        q = T(fma(-T(alpha), q, m.R[e]));
+        m.R[e] = q;
+    }
+    __syncthreads();
+}
+
+// W = z^ = M^-1 r^ for the spectrum r^ in W; returns r.z.
+template <typename T, typename M>
+__device__ __forceinline__ double precondition(const SmallArgs<T> &a, const M &m, int &turn) {
     constexpr int NC = 4;
     double acc = 0.0;
     for (int s = threadIdx.x; s < a.nspec; s += NT) {
@@ -435,11 +453,7 @@ __device__ __forceinline__ double residual_step(const SmallArgs<T> &a, const M &
         Cx<T> *x = m.W + slot_at<T>(a, s, wt);
         Cx<T> r[DIM], z[DIM];
         #pragma unroll
-        for (int c = 0; c < DIM; ++c) {
-            Cx<T> &h = m.Rh[c * a.nspec + s];
-            r[c] = STEP ? Cx<T>{h.x - alpha * x[c].x, h.y - alpha * x[c].y} : x[c];
-            h = r[c];
-        }
+        for (int c = 0; c < DIM; ++c) r[c] = x[c];
         double d;
         if (a.table_lds) {
             d = slot_solve<T>(m.tab + s, a.nspec, r, z);
@@ -463,7 +477,7 @@ __device__ __forceinline__ void direction(const SmallArgs<T> &a, const M &m, T b
         const int c = (int)a.d_N.div((uint32_t)e), v = e - c * a.N;
         const int row = (int)a.d_last.div((uint32_t)v), i = v - row * a.nlast;
         const T z = w[real_at<T>(a, row, i, c)] * sc;
-        m.P[e] = beta == T(0) ? z : z + beta * m.P[e];
+        m.P[e] = beta == T(0) ? z : fma(beta, m.P[e], z);
     }
     __syncthreads();
 }
@@ -519,12 +533,13 @@ __global__ __launch_bounds__(NT) void k_small_solve(SmallArgs<T> a) {
                 column(s.end[k], s.axis[k], e);
                 column(s.start[k], s.axis[k], b);
                 #pragma unroll
-                for (int i = 0; i < DIM; ++i) q[i] += (e[i] - b[i]) * a.ih[s.axis[k]];
+                for (int i = 0; i < DIM; ++i) q[i] = fma(e[i] - b[i], a.ih[s.axis[k]], q[i]);
             }
             const int row = (int)a.d_last.div((uint32_t)v), i0 = v - row * a.nlast;
             #pragma unroll
             for (int i = 0; i < DIM; ++i) {
                 put_real<T>(a, w, row, i0, i, LOAD ? -q[i] : q[i]);
+                if constexpr (LOAD) m.R[i * a.N + v] = -q[i];
                 if constexpr (!LOAD) acc += double(p[0][i]) * double(q[i]);
             }
         }
@@ -534,7 +549,7 @@ __global__ __launch_bounds__(NT) void k_small_solve(SmallArgs<T> a) {
     apply(std::true_type{});
     __syncthreads();
     forward<T>(a, m.W, m.tw, m.pass);
-    double rho = residual_step<false>(a, m, T(0), turn);
+    double rho = precondition(a, m, turn);
     const double ref = rho;
     double relres = 0.0, pq = 0.0, alpha = 0.0, beta = 0.0;
     int iters = 0, status = FEH_OK;
@@ -559,9 +574,10 @@ __global__ __launch_bounds__(NT) void k_small_solve(SmallArgs<T> a) {
             break;
         }
         alpha = rho / pq;
+        advance(a, m, alpha);
         forward<T>(a, m.W, m.tw, m.pass);
-        const double r = residual_step<true>(a, m, T(alpha), turn);
-        for (int e = threadIdx.x; e < DIM * a.N; e += NT) m.X[e] += U(alpha) * U(m.P[e]);
+        const double r = precondition(a, m, turn);
+        for (int e = threadIdx.x; e < DIM * a.N; e += NT) m.X[e] = fma(U(alpha), U(m.P[e]), m.X[e]);
         ++iters;
         if (!isfinite(r)) {
             status = FEH_EBREAKDOWN;
@@ -647,6 +663,7 @@ __global__ __launch_bounds__(NT) void k_small_finite(SmallArgs<T> a) {
             for (int i = 0; i < DIM; ++i) {
                 const T qv = T(TAN ? a.w * q[i] : -a.w * q[i]);
                 put_real<T>(a, w, row, i0, i, qv);
+                if constexpr (!TAN) m.R[i * a.N + v] = qv;
                 if constexpr (TAN) acc += double(p[0][i]) * double(qv);
             }
             if constexpr (!TAN) {
@@ -684,7 +701,7 @@ __global__ __launch_bounds__(NT) void k_small_finite(SmallArgs<T> a) {
         for (int it = 0; it < a.max_newton; ++it) {
             const double nP = sqrt(all_sum(apply(std::false_type{}), m.red, turn));
             forward<T>(a, m.W, m.tw, m.pass);
-            double rho = residual_step<false>(a, m, T(0), turn);
+            double rho = precondition(a, m, turn);
             const double nG = sqrt(rho / a.w);
             rel_eq = nP > 0.0 ? nG / nP : 0.0;
             if (nG <= a.equil_tol * nP) {
@@ -703,9 +720,10 @@ __global__ __launch_bounds__(NT) void k_small_finite(SmallArgs<T> a) {
                 const double pq = all_sum(apply(std::true_type{}), m.red, turn);
                 if (!(pq > 0.0) || !isfinite(pq)) break;
                 const double alpha = rho / pq;
+                advance(a, m, alpha);
                 forward<T>(a, m.W, m.tw, m.pass);
-                const double r = residual_step<true>(a, m, T(alpha), turn);
-                for (int e = threadIdx.x; e < DIM * a.N; e += NT) m.X[e] += alpha * double(m.P[e]);
+                const double r = precondition(a, m, turn);
+                for (int e = threadIdx.x; e < DIM * a.N; e += NT) m.X[e] = fma(alpha, double(m.P[e]), m.X[e]);
                 ++iters;
                 if (!isfinite(r)) break;
                 const double rr = r > 0.0 ? r : 0.0;

@@ -67,3 +67,34 @@ def test_one_workgroup_finite_strain(kind, shape, prec):
         assert p["status"] == q["status"] == 0 and abs(p["newton_iterations"] - q["newton_iterations"]) <= 1
     assert float((a["F"] - b["F"]).abs().max()) <= 10 * tol
     assert rel(a["P_mean"], b["P_mean"]) <= 100 * tol
+
+
+@pytest.mark.parametrize("shape", [(32, 32), (40, 20), (300, 4), (4, 300), (900, 2), (1024, 2), (31, 31), (17, 31)])
+def test_residual_keeps_falling_in_fp32(shape):
+    """The residual of an FP32 solve keeps to that of the general path well
+    below the rounding of the first residual (6e-8), where nothing but the
+    rounding of the day may enter it: at 1e-6 and 1e-7 both stop within an
+    iteration of one another, and the displacements agree to FP32's rounding
+    times the grid's length (the smallest eigenvalue's share of a long wave)."""
+    import paper_2105_03297_amd as feh
+    say("small fp32 residual", shape)
+    lam, mu = random_material(shape, 12, "fp32")
+    A = np.random.default_rng(2).standard_normal((2, 2, 2)) * 0.01
+    Eb = 0.5 * (A + np.swapaxes(A, 1, 2))
+    for tol in (1e-6, 1e-7):
+        out = []
+        for general in (False, True):
+            h = feh.Homogenizer(shape, n_load=2, precision="fp32")
+            if general:
+                feh.feh_plan_set_tuning(h.plan, feh.feh_plan_tuning(h.plan))
+            h.set_material(lam=lam, mu=mu)
+            o = h.solve(Eb, tol=tol, max_iter=200, return_u=True)
+            out.append(o)
+            h.close()
+        a, b = out
+        assert all(r["status"] == 0 for r in b["report"])
+        for x, y in zip(a["report"], b["report"]):
+            assert x["status"] == 0 and abs(x["iterations"] - y["iterations"]) <= 1, (tol, x, y)
+        ua, ub = (o["u"].double().cpu().numpy() for o in out)
+        for l in range(2):
+            assert np.linalg.norm(ua[l] - ub[l]) <= 6e-8 * max(shape) * 10 * np.linalg.norm(ub[l])
