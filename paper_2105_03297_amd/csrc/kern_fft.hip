@@ -1474,13 +1474,14 @@ __global__ __launch_bounds__(kFftThreads) void k_first_table(FK<T> a) {
 // (TAB) or formed again per load case just in time.  The power-of-two PERLC
 // instantiations are held to 3 waves per SIMD (at most 168 VGPRs, no spills).
 template <typename T, int PPT, int DIM, int MODE, int GEN, bool PERLC, bool TAB>
-__global__ __launch_bounds__(kFftThreads) __attribute__((amdgpu_waves_per_eu((PERLC && !GEN) ? 3 : 1))) void k_first(FK<T> a) {
+__global__ __launch_bounds__(kFftThreads) __attribute__((amdgpu_waves_per_eu((PERLC && !GEN) ? 3 : TAB ? kGenWaves<T, GEN> : 1))) void k_first(FK<T> a) {
     constexpr int NT = kFftThreads;
     constexpr int D = DIM;
     constexpr int KW = (PPT + D - 1) / D;  // wavevector slots per thread: PB n0 <= PPT NT / D
     constexpr int KC = PERLC ? 1 : KW;     // cached slots
-    __shared__ Cx<T> buf[PPT * NT];
+    __shared__ Cx<T> sbuf[GEN ? 1 : PPT * NT];
     __shared__ double red[NT / 64];
+    Cx<T> *buf = GEN ? reinterpret_cast<Cx<T> *>(feh_dyn_lds) : sbuf;
     int blk, lc0, lc1;
     if constexpr (PERLC) {
         const int t = xcd_remap(blockIdx.x, a.total);
@@ -1500,12 +1501,13 @@ __global__ __launch_bounds__(kFftThreads) __attribute__((amdgpu_waves_per_eu((PE
     const long long in0 = (long long)blk * PB;
     const int lim = (int)min((long long)PB, inner - in0) * D;
     const int cnt = nb * n0;
-    // dynamic LDS: twiddles of axis 0, then (mode 0) the phase factors of this
-    // block's PB inner wavevector indices; the axis-0 phase factors are read
-    // from the plan's tables (once per wavevector slot, L2-resident)
-    Cx<T> *twl = reinterpret_cast<Cx<T> *>(feh_dyn_lds);
+    // dynamic LDS: the tile of general lengths, twiddles of axis 0, then (mode
+    // 0) the phase factors of this block's PB inner wavevector indices; the
+    // axis-0 phase factors are read from the plan's tables (once per
+    // wavevector slot, L2-resident)
+    Cx<T> *twl = reinterpret_cast<Cx<T> *>(feh_dyn_lds) + (GEN ? a.lbuf : 0);
     const int tw_bytes = ((n0 * (int)sizeof(Cx<T>) + 15) / 16) * 16;
-    Cx<double> *pin = reinterpret_cast<Cx<double> *>(reinterpret_cast<char *>(feh_dyn_lds) + tw_bytes);  // [PB][4]: aa1, om1, aa2, om2 (2D: aa1, om1)
+    Cx<double> *pin = reinterpret_cast<Cx<double> *>(reinterpret_cast<char *>(twl) + tw_bytes);  // [PB][4]: aa1, om1, aa2, om2 (2D: aa1, om1)
     stage(twl, a.tw, n0);
     // per cached slot: real diagonal of M^-1, then its upper triangle (complex)
     T Mid[KC][D];
@@ -1631,7 +1633,7 @@ __global__ __launch_bounds__(kFftThreads) __attribute__((amdgpu_waves_per_eu((PE
 // Pencils per block of the compile-time first-axis pass (N = n0): N PB D
 // points per workgroup, 24 per thread in FP32 3D.
 template <typename T, int N>
-constexpr int ct_first_pencils() { return (sizeof(T) == 4 ? 2048 : 1024) / N; }
+constexpr int ct_first_pencils() { return N == 1024 ? 2 : (sizeof(T) == 4 ? 2048 : 1024) / N; }
 
 // First axis with the compile-time transform, the CG's fused pass only
 // (forward, z = M^-1 r with the inverse table and the Parseval partial,
@@ -1666,7 +1668,9 @@ __global__ __launch_bounds__(kFftThreads) void k_first_ct(FK<T> a) {
     constexpr bool FUSE_LAST = SL >= 1 && KB >= 1 && KB * RL == NR && ct_lstar(N, SL) * RL == N;
     __shared__ Cx<T> buf[N * NB];
     __shared__ Cx<T> twl[N];
-    __shared__ double red[NT / 64];
+    // the partial sums of the last step take the twiddles' place: two FP64
+    // 1024-point workgroups then fill a CU's LDS to the byte
+    double *red = reinterpret_cast<double *>(twl);
     const int t = xcd_remap(blockIdx.x, a.total);
     const int blk = t / a.L;
     const int lc = t - blk * a.L;
@@ -2162,9 +2166,15 @@ int first_t(const feh_plan &p, const FftArgs &fa, int mode) {
     const bool perlc = table ? first_by_table(p) : first_per_load_case(p);
     a.total = perlc ? a.nblk * p.L : a.nblk;  // one block per (load case, pencils) or per pencils
     dim3 g(a.total), b(kFftThreads);
-    const size_t dyn = ((a.n0 * sizeof(Cx<T>) + 15) / 16) * 16 + (mode == 0 ? 4 * (size_t)PB * sizeof(Cx<double>) : 0);
-    if ((small ? ppt<T, true>() : PPT) * kFftThreads * sizeof(Cx<T>) + (kFftThreads / 64) * sizeof(double) + dyn > kLdsPerWorkgroup)
+    const size_t tab_dyn = ((a.n0 * sizeof(Cx<T>) + 15) / 16) * 16 + (mode == 0 ? 4 * (size_t)PB * sizeof(Cx<double>) : 0);
+    if ((small ? ppt<T, true>() : PPT) * kFftThreads * sizeof(Cx<T>) + (kFftThreads / 64) * sizeof(double) + tab_dyn > kLdsPerWorkgroup)
         return set_error(FEH_ENOTSUP, "first axis too long for the LDS transform");
+    // general lengths: a tile of the pass's own size, 16 bytes a multiple (see
+    // lds_of_pass); with the largest tile one FP64 workgroup of 1661 points
+    // had a CU to itself (1661^2 by strains, a solve: 19.7 -> 16.7 ms)
+    constexpr int kAlign = 16 / (int)sizeof(Cx<T>);
+    a.lbuf = pow2_len(a.n0) ? 0 : (a.n0 * PB * DIM + kAlign - 1) / kAlign * kAlign;
+    const size_t dyn = (size_t)a.lbuf * sizeof(Cx<T>) + tab_dyn;
     // the CG's fused pass (element volume relative to the voxel) reads the
     // (B^*B)^-1 table, built here on the first use for this workspace and
     // block size; the test exports (true volume) form the inverses in place
@@ -2181,6 +2191,9 @@ int first_t(const feh_plan &p, const FftArgs &fa, int mode) {
         case 64: hipLaunchKernelGGL((k_first_ct<T, 64, DIM>), g, b, 0, p.stream, a); break;
         case 128: hipLaunchKernelGGL((k_first_ct<T, 128, DIM>), g, b, 0, p.stream, a); break;
         case 256: hipLaunchKernelGGL((k_first_ct<T, 256, DIM>), g, b, 0, p.stream, a); break;
+        case 1024:
+            if constexpr (sizeof(T) == 4 || DIM == 2) hipLaunchKernelGGL((k_first_ct<T, 1024, DIM>), g, b, 0, p.stream, a);
+            break;
         default: hipLaunchKernelGGL((k_first_ct<T, 512, DIM>), g, b, 0, p.stream, a); break;
         }
         return hip_check(hipGetLastError(), "first-axis fft launch");
@@ -2222,18 +2235,23 @@ bool first_per_load_case(const feh_plan &p) {
 }
 
 // Pencils per block of the compile-time first-axis pass of the CG, or 0 when
-// the plan's shape or schedule has none: a power-of-two axis 0 of 64 to 512
-// points in the default radix order, the default layout (one workgroup
+// the plan's shape or schedule has none: a power-of-two axis 0 of 64 to 1024
+// points (1024: FP64 in 2D only) in the default radix order, the default layout (one workgroup
 // per load case) and block size, and offsets that fit the 24-bit products
 // of the staging.
 int first_ct_pencils(const feh_plan &p) {
     const int n0 = (int)p.n[0];
     if (!p.tune_ct || p.tune_pb_first != 0 || !first_per_load_case(p)) return 0;
-    if (!(n0 == 64 || n0 == 128 || n0 == 256 || n0 == 512) || !ct_schedule_matches(p.fft[0], n0)) return 0;
+    // 1024 points: two pencils, at most half a CU's LDS.  The run-time pass's
+    // tile and twiddles took just more than half of it in FP64, so that each of
+    // its workgroups had a CU to itself (1024^2 x 3 load cases: a pass 78 us,
+    // a solve 27.6 -> 22.7 ms)
+    const bool two = n0 == 1024 && (p.prec == FEH_FP32 || p.dim == 2);
+    if (!(n0 == 64 || n0 == 128 || n0 == 256 || n0 == 512 || two) || !ct_schedule_matches(p.fft[0], n0)) return 0;
     const long long inner = p.dim == 3 ? p.n[1] * p.nh : p.nh;
     const long long rowD = inner * p.dim;
     if (rowD >= (1 << 24) || rowD * n0 >= (1ll << 31)) return 0;
-    return (p.prec == FEH_FP32 ? 2048 : 1024) / n0;
+    return two ? 2 : (p.prec == FEH_FP32 ? 2048 : 1024) / n0;
 }
 
 int first_pencils_default(const feh_plan &p) {
