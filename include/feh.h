@@ -252,7 +252,8 @@ int feh_plan_tuning(const feh_plan *plan, int *values, int n_values);
  * transformed length (n_a, n_last/2 for an even last axis), and optionally
  * the trailing compile-time transform flag (0 or 1; kept if absent).
  * FEH_EINVAL leaves the plan unchanged.  Any valid schedule is exact to
- * rounding. */
+ * rounding.  A plan whose schedule was set runs it also where a small 2D grid
+ * would otherwise be solved by one workgroup per load case, in one launch. */
 int feh_plan_set_tuning(feh_plan *plan, const int *values, int n_values);
 
 /* Whether the plan's CG, with its current schedule, keeps the residual as its
@@ -379,7 +380,7 @@ int feh_strain_cg_points(int kind, int dim, int *n_points);
 /* Device workspace bytes of feh_strain_cg_solve for this plan and kind: the
  * strain-space Krylov vectors x, r, p, q (n_load * n_e * nsym * N reals each,
  * nsym = 3 in 2D, 6 in 3D), their half spectrum, CG scalars and partial
- * sums. */
+ * sums.  (FEH_DERIV_FE runs on nodal vectors, which take less of it.) */
 int feh_strain_cg_workspace_bytes(const feh_plan *plan, int kind, size_t *bytes);
 
 /* Projected CG in strain space (Sec. "Compatibility projection": CG on
@@ -426,7 +427,8 @@ typedef struct {
 
 /* Device workspace bytes of feh_finite_strain_solve: five deformation-gradient
  * fields (F, dF and the CG vectors r, p, q; n_load * n_e * D^2 * N reals each),
- * their half spectrum, CG scalars and partial sums. */
+ * their half spectrum, CG scalars and partial sums.  (The stencil kinds FE,
+ * FD, CD and LS run on nodal vectors, which take less of it.) */
 int feh_finite_strain_workspace_bytes(const feh_plan *plan, int kind, size_t *bytes);
 
 /* Finite-strain homogenization (Sec. "Compatibility projection"): find the

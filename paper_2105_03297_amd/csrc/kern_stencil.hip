@@ -333,7 +333,7 @@ __global__ __launch_bounds__((Tile<DIM, VYT>::NT)) __attribute__((amdgpu_waves_p
     // edge fluxes passed through LDS, one column per voxel: in 3D only the 18
     // values the next row of voxels needs (the left neighbour's come by DPP);
     // with the x- and z-edge fluxes raw (24 values) FP64 128^3 x 6 load cases
-    // took 309 us, now 289, at 600 MB of traffic: bound by the two waves per
+    // took 309 us, now 289, at 0.9 GB of traffic: bound by the two waves per
     // SIMD that its 200 registers allow (three, at 168, spill: 290)
     constexpr int NX = DIM == 3 ? 18 : NQ;
     __shared__ CT Es[NX][NT];
