@@ -34,8 +34,11 @@ extern __shared__ double feh_dyn_lds[];
 // FP64 transforms of general lengths (radix 3..13 and direct passes) are held
 // to at most 256 VGPRs, two waves per SIMD; with tiles sized to the pass, two
 // workgroups then fit a CU for rows of up to about 1700 points.
+// So are the FP32 ones with a prime pass (GEN = 2), whose accumulators else
+// take 270 to 340 (FP32, 24 iterations of 6 load cases: 85 x 95 x 115
+// 32.9 -> 20.7 ms, 101 x 97 x 89 34.0 -> 21.7, 68^3 8.6 -> 6.9).
 template <typename T, int GEN>
-constexpr int kGenWaves = (GEN != 0 && sizeof(T) == 8) ? 2 : 1;
+constexpr int kGenWaves = (GEN != 0 && sizeof(T) == 8) || GEN == 2 ? 2 : 1;
 
 // LDS one workgroup may hold on gfx950 (160 KiB).  Every launch checks its
 // static plus dynamic LDS against it on the host and reports FEH_ENOTSUP
