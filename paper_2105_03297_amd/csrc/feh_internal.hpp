@@ -336,6 +336,15 @@ int precondition(const feh_plan &p, const void *r, void *z, double *partial, con
                  void *rhat = nullptr);
 int cg_iteration(const feh_plan &p, LcState *st, double tol, int max_iter);
 
+// Finite strain on nodal vectors (finite.hip): byte offsets in the caller's
+// buffer of the CG's vectors (u the increment), the displacement fluctuation
+// and the Newton mask, and the stride of the partial sums' rows.
+struct FiniteWork {
+    NodalWork cg;
+    size_t u, nmask, part_stride, total;
+};
+FiniteWork finite_layout(const feh_plan &p, int kind);
+
 // Stencil derivatives on nodal fields (kern_nodal.hip): the tangent and the
 // residual of the Saint Venant-Kirchhoff law at F = Fbar + B u.  Every launch
 // leaves nodal_num_parts partial sums a row, part_stride apart.
@@ -374,6 +383,7 @@ int launch_small_finite(const feh_plan &p, int kind, const SmallFinite &f);
 int stencil_num_parts(const feh_plan &p);
 int stencil_rows(const feh_plan &p);           // 3D stencil tile rows in use
 int first_num_parts(const feh_plan &p);
+int first_num_parts(const feh_plan &p, int metric);  // under another metric than the plan's
 int first_pencils_default(const feh_plan &p);  // before tuning
 int first_ct_pencils(const feh_plan &p);       // compile-time CG pass block size (0: none)
 bool first_per_load_case(const feh_plan &p);   // axis-0 pass layout (workgroup per load case)

@@ -398,17 +398,14 @@ FLayout make_flayout(const feh_plan &p, int ne) {
     return Lo;
 }
 
-// The nodal form's vectors in the caller's buffer: the CG's (u the increment),
-// the displacement fluctuation and the Newton mask.
-struct NLayout {
-    NodalWork cg;
-    size_t u, nmask, part_stride, total;
-};
+}  // namespace
 
-NLayout make_nlayout(const feh_plan &p) {
-    NLayout n{};
+FiniteWork finite_layout(const feh_plan &p, int kind) {
+    FiniteWork n{};
     n.cg = nodal_layout(p);
-    n.part_stride = (size_t)std::max({nodal_num_parts(p), first_num_parts(p), stencil_num_parts(p)});
+    // the first-axis pass as it runs under the solve's metric, whose inverses
+    // come from the table whatever layout the plan's schedule asks for
+    n.part_stride = (size_t)std::max({nodal_num_parts(p), first_num_parts(p, 1 + kind), stencil_num_parts(p)});
     size_t o = n.cg.total;
     auto take = [&](size_t b) {
         const size_t at = o;
@@ -423,11 +420,13 @@ NLayout make_nlayout(const feh_plan &p) {
     return n;
 }
 
+namespace {
+
 // Bytes asked of the caller: the deformation-gradient fields, in which the
 // nodal form has room (a plan too small for that asks for what it needs).
 size_t fs_work_bytes(const feh_plan &p, int kind, int ne) {
     const size_t b = make_flayout(p, ne).total;
-    return nodal_kind(kind, p.dim) ? std::max(b, make_nlayout(p).total) : b;
+    return nodal_kind(kind, p.dim) ? std::max(b, finite_layout(p, kind).total) : b;
 }
 
 struct FRun {
@@ -640,7 +639,7 @@ int fs_solve_t(FRun &R, const double *Fbar_host, const FsParams &prm, void *Fout
 // outside the compatible fields and one projection does.  u and du are kept
 // in double: F is formed from u at every use, and an FP32 plan's F carries no
 // rounding of its own.
-int fs_solve_nodal(feh_plan &p, int kind, char *work, const NLayout &Lo, const double *Fbar_host, const FsParams &prm,
+int fs_solve_nodal(feh_plan &p, int kind, char *work, const FiniteWork &Lo, const double *Fbar_host, const FsParams &prm,
                    void *Fout, void *Pout, FsOut &out) {
     const int L = p.L, D = p.dim, DD = D * D;
     NodalScope scope(p, work, Lo.cg);
@@ -825,7 +824,7 @@ int feh_finite_strain_solve(feh_plan *plan, int kind, const double *Fbar_host, i
         FsOut out;
         int rc;
         if (nodal_kind(kind, D))
-            rc = fs_solve_nodal(p, kind, R.w, make_nlayout(p), Fbar_host, prm, F_dev, P_dev, out);
+            rc = fs_solve_nodal(p, kind, R.w, finite_layout(p, kind), Fbar_host, prm, F_dev, P_dev, out);
         else if (p.prec == FEH_FP64)
             rc = D == 3 ? fs_solve_t<double, 3>(R, Fbar_host, prm, F_dev, P_dev, out)
                         : fs_solve_t<double, 2>(R, Fbar_host, prm, F_dev, P_dev, out);

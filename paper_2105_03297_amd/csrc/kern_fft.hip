@@ -2093,14 +2093,17 @@ int first_plain_t(const feh_plan &p, const FftArgs &fa, bool inverse) {
     return launch_middle_tile<T>(p, a, small, inverse, "first-axis fft launch");
 }
 
-// The CG's first-axis pass reads its inverses from the table.
-bool first_by_table(const feh_plan &p) { return first_per_load_case(p) || p.metric != 0 || p.tune_first_perlc == 0; }
+// The CG's first-axis pass reads its inverses from the table (the only place
+// of those of a metric other than 0).
+bool first_by_table(const feh_plan &p, int metric) {
+    return first_per_load_case(p) || metric != 0 || p.tune_first_perlc == 0;
+}
 
 // Whether the CG's run-time first-axis pass takes the small tile, and its
 // pencils (at least a quarter of the default: the partial sums have one slot a
 // pencil block of that size).  *PB: the full tile's pencils.
-bool first_small_pencils(const feh_plan &p, int *PB) {
-    if (p.tune_pb_first != 0 || !first_by_table(p) || first_ct_pencils(p)) return false;
+bool first_small_pencils(const feh_plan &p, int metric, int *PB) {
+    if (p.tune_pb_first != 0 || !first_by_table(p, metric) || first_ct_pencils(p)) return false;
     const int points = (p.prec == FEH_FP32 ? ppt<float, true>() : ppt<double, true>()) * kFftThreads;
     const long long inner = p.dim == 3 ? p.n[1] * p.nh : p.nh;
     const int least = std::min(*PB, std::max(1, first_pencils_default(p) / 4));
@@ -2153,11 +2156,13 @@ int first_t(const feh_plan &p, const FftArgs &fa, int mode) {
     // a grid with fewer pencils than one block
     if (ctpb > 0) PB = ctpb;
     else if (PB > a.inner_total) PB = (int)a.inner_total;
-    const bool small = mode == 0 && fa.unit_volume && first_small_pencils(p, &PB);
+    const bool small = mode == 0 && fa.unit_volume && first_small_pencils(p, p.metric, &PB);
     a.PB = PB;
     a.d_PB = FastDiv::make((uint32_t)PB);
     a.nbd = FastDiv::make((uint32_t)(PB * DIM));
     a.nblk = (int)((a.inner_total + PB - 1) / PB);
+    if (fa.partial && (size_t)a.nblk > p.part_stride)
+        return set_error(FEH_EINVAL, "first axis: more partial sums than a row of them holds");
     // The CG's pass, unless the layout was set: one workgroup per load case at
     // every length.  It reads the inverses from the table (the only place of
     // the metrics other than M), so it has n_load times the workgroups of the
@@ -2166,7 +2171,7 @@ int first_t(const feh_plan &p, const FftArgs &fa, int mode) {
     // 160^3 44.0 -> 37.0; FP64 2D: 151^2 25.1 -> 13.4, 300^2 5.2 -> 3.7,
     // 900^2 9.9 -> 10.0).
     const bool table = mode == 0 && fa.unit_volume;
-    const bool perlc = table ? first_by_table(p) : first_per_load_case(p);
+    const bool perlc = table ? first_by_table(p, p.metric) : first_per_load_case(p);
     a.total = perlc ? a.nblk * p.L : a.nblk;  // one block per (load case, pencils) or per pencils
     dim3 g(a.total), b(kFftThreads);
     const size_t tab_dyn = ((a.n0 * sizeof(Cx<T>) + 15) / 16) * 16 + (mode == 0 ? 4 * (size_t)PB * sizeof(Cx<double>) : 0);
@@ -2265,7 +2270,9 @@ int first_pencils_default(const feh_plan &p) {
     return PB;
 }
 
-int first_num_parts(const feh_plan &p) {
+int first_num_parts(const feh_plan &p) { return first_num_parts(p, p.metric); }
+
+int first_num_parts(const feh_plan &p, int metric) {
     int PB = first_pencils_default(p);
     // tuned value, never below a quarter of the default: the partial-sum
     // buffer holds one slot per pencil block for that size
@@ -2273,7 +2280,7 @@ int first_num_parts(const feh_plan &p) {
     if (const int ct = first_ct_pencils(p)) PB = ct;  // the CG's fused pass
     const long long inner = p.dim == 3 ? p.n[1] * p.nh : p.nh;
     if (PB > inner) PB = (int)inner;
-    (void)first_small_pencils(p, &PB);
+    (void)first_small_pencils(p, metric, &PB);
     return (int)((inner + PB - 1) / PB);
 }
 
