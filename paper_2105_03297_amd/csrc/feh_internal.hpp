@@ -337,11 +337,12 @@ int precondition(const feh_plan &p, const void *r, void *z, double *partial, con
 int cg_iteration(const feh_plan &p, LcState *st, double tol, int max_iter);
 
 // Finite strain on nodal vectors (finite.hip): byte offsets in the caller's
-// buffer of the CG's vectors (u the increment), the displacement fluctuation
-// and the Newton mask, and the stride of the partial sums' rows.
+// buffer of the CG's vectors (u the increment), the displacement fluctuation,
+// the Newton mask and the one-workgroup solve's outcome ([L][5] doubles), and
+// the stride of the partial sums' rows.
 struct FiniteWork {
     NodalWork cg;
-    size_t u, nmask, part_stride, total;
+    size_t u, nmask, outcome, part_stride, total;
 };
 FiniteWork finite_layout(const feh_plan &p, int kind);
 

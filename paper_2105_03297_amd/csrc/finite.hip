@@ -416,6 +416,9 @@ FiniteWork finite_layout(const feh_plan &p, int kind) {
     n.nmask = take((size_t)p.L * sizeof(int));
     n.cg.part = take((size_t)p.L * p.dim * p.dim * n.part_stride * sizeof(double));
     n.cg.sums = take((size_t)p.L * 9 * sizeof(double));
+    // in the increment's place, which that solve keeps in LDS: D N doubles a
+    // load case, at least 8
+    n.outcome = n.cg.u;
     n.total = o;
     return n;
 }
@@ -672,12 +675,13 @@ int fs_solve_nodal(feh_plan &p, int kind, char *work, const FiniteWork &Lo, cons
     out.rel_inc.assign(L, 0.0);
     std::vector<double> fb(L * DD), h;
     if (small_solve_ok(p, true)) {
-        // one launch; its outputs in the partial sums, which it does not use
+        // one launch, which reads Fbar from the sums
+        double *outcome = reinterpret_cast<double *>(work + Lo.outcome);
         CK(hip_check(hipMemcpyAsync(sums, Fbar_host, L * DD * sizeof(double), hipMemcpyHostToDevice, p.stream), "upload Fbar"));
-        const SmallFinite f{prm.n_steps, prm.max_newton, prm.max_cg, prm.newton_tol, prm.equil_tol, prm.cg_tol, sums, fbar, u, part};
+        const SmallFinite f{prm.n_steps, prm.max_newton, prm.max_cg, prm.newton_tol, prm.equil_tol, prm.cg_tol, sums, fbar, u, outcome};
         CK(launch_small_finite(p, kind, f));
         h.resize(5 * L);
-        CK(hip_check(hipMemcpyAsync(h.data(), part, h.size() * sizeof(double), hipMemcpyDeviceToHost, p.stream), "read outcome"));
+        CK(hip_check(hipMemcpyAsync(h.data(), outcome, h.size() * sizeof(double), hipMemcpyDeviceToHost, p.stream), "read outcome"));
         CK(hip_check(hipStreamSynchronize(p.stream), "finite strain"));
         for (int l = 0; l < L; ++l) {
             out.newton[l] = (int)h[5 * l];

@@ -30,6 +30,19 @@ static void look(const std::vector<int64_t> &n, int prec, int n_load, int layout
                   n.size() == 3 ? (int)n[2] : 1, prec, n_load, layout, kind);
     if (w.total > bytes) std::printf("%s: %zu bytes in a buffer of %zu\n", name, w.total, bytes);
     {
+        // the one-workgroup solve's outcome is written while other workgroups
+        // still read Fbar (in the sums) and has to leave alone what it returns besides
+        const size_t D = p.dim, from = w.outcome, to = from + 5 * p.L * sizeof(double);
+        const struct {
+            const char *what;
+            size_t at, bytes;
+        } others[] = {{"Fbar", w.cg.sums, p.L * D * D * 8}, {"the last Fbar", w.cg.ebar, p.L * D * D * 8},
+                      {"u", w.u, p.L * D * (size_t)p.N * 8}};
+        for (const auto &x : others)
+            if (from < x.at + x.bytes && x.at < to) std::printf("%s: outcome runs into %s\n", name, x.what);
+        if (to > w.total) std::printf("%s: outcome past the buffer\n", name);
+    }
+    {
         // as the solve runs: no kernel may leave more sums a row than the rows are apart
         NodalScope scope(p, reinterpret_cast<char *>(size_t(1) << 40), w.cg);
         p.part_stride = w.part_stride;
@@ -46,11 +59,11 @@ static void look(const std::vector<int64_t> &n, int prec, int n_load, int layout
 int main() {
     const std::vector<std::vector<int64_t>> shapes = {
         {9, 40, 40}, {10, 12, 12}, {9, 2001}, {8, 40, 40}, {16, 12, 12}, {4, 2001}, {64, 48, 48}, {128, 9, 10},
-        {2, 2}, {2, 15}, {3, 2}, {17, 17}, {64, 64}, {512, 3}, {1024, 64}, {31, 33}, {2, 2, 2}, {2, 2, 31},
+        {2, 2}, {2, 3}, {2, 4}, {2, 7}, {2, 8}, {2, 9}, {2, 14}, {2, 15}, {2, 16}, {3, 2}, {17, 17}, {64, 64}, {512, 3}, {1024, 64}, {31, 33}, {2, 2, 2}, {2, 2, 31},
         {45, 50, 39}, {3, 300, 5}, {128, 128, 128}};
     for (const auto &n : shapes)
         for (int prec : {FEH_FP64, FEH_FP32})
-            for (int n_load : {1, 2, 13, 64})
+            for (int n_load : {1, 2, 6, 7, 13, 16, 64})
                 for (int layout : {-1, 0, 1})
                     for (int kind : {FEH_DERIV_FE, FEH_DERIV_FD, FEH_DERIV_CD, FEH_DERIV_LS})
                         if (nodal_kind(kind, (int)n.size())) look(n, prec, n_load, layout, kind);
