@@ -216,9 +216,9 @@ int feh_solve_noalloc(feh_plan *plan, const void *lambda_dev, const void *mu_dev
  * candidate radix orders of each axis (the orders of the default
  * factorisation and of the radix-4 one) and then fewer rows / pencils per
  * workgroup (1/2, 1/4 of the default) for the last, middle and first axis
- * passes and the two workgroup layouts of the first-axis pass (every load
- * case in one workgroup with the per-wavevector inverses kept in registers,
- * or one workgroup per load case forming them again) and, in 3D, the two
+ * passes and, for a power-of-two first axis, the two workgroup layouts of its
+ * pass (every load case in one workgroup with the per-wavevector inverses kept
+ * in registers, or one workgroup per load case reading them) and, in 3D, the two
  * stencil tile heights (8 or 16 rows of 32 voxels), each over `reps` runs
  * (< 1: 3), and keeps the fastest.  The
  * transforms stay exact to rounding whatever is chosen; repeated solves on
@@ -231,8 +231,9 @@ int feh_plan_autotune(feh_plan *plan, int reps);
  * pencils per workgroup (axis 1), pencils per workgroup (axis 0) (0 =
  * default heuristic), axis-0 workgroup layout (1: one workgroup per load
  * case, the default for a power-of-two axis 0; 0: every load case in one
- * workgroup, the default otherwise; a plan whose schedule was never set or
- * tuned takes 1 for the CG's pass at every length), stencil tile rows (3D: 8 or
+ * workgroup, the default otherwise, where it is the layout of the passes that
+ * form their inverses: the CG's, which reads them from a table, takes one
+ * workgroup per load case at those lengths always), stencil tile rows (3D: 8 or
  * 16 rows of 32 voxels; 2D: 1)], then for each axis 0..2 the
  * number of passes followed by the radices in pass order, then 1 if passes
  * whose shape has a compile-time transform may use it (power-of-two axes of

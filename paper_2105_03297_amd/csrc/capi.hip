@@ -1268,10 +1268,13 @@ int feh_plan_autotune(feh_plan *plan, int reps) {
             CK(tune_axis(0, (int)p.n[0], [&]() -> int { return launch_first_fused(p, fa); }, &p.tune_pb_first, pb,
                          std::max(1, pb / 4)));
             // workgroup layout of the axis-0 pass: all load cases per workgroup
-            // (inverses cached in registers) or one workgroup per load case
+            // (inverses cached in registers) or one workgroup per load case; at
+            // other lengths than powers of two the CG's pass has the latter only
+            const bool pow2 = (p.n[0] & (p.n[0] - 1)) == 0;
             double best = 1e30;
-            int keep = 0;
+            int keep = p.tune_first_perlc;
             for (int v : {-1, 1}) {
+                if (!pow2) break;
                 p.tune_first_perlc = v;
                 double ms = 0;
                 CK(time_runs(p, [&]() -> int { return launch_first_fused(p, fa); }, reps, ms));

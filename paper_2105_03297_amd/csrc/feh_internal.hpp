@@ -388,6 +388,7 @@ int first_num_parts(const feh_plan &p, int metric);  // under another metric tha
 int first_pencils_default(const feh_plan &p);  // before tuning
 int first_ct_pencils(const feh_plan &p);       // compile-time CG pass block size (0: none)
 bool first_per_load_case(const feh_plan &p);   // axis-0 pass layout (workgroup per load case)
+bool first_by_table(const feh_plan &p, int metric);  // the CG's axis-0 pass reads the inverse table
 int post_num_parts(const feh_plan &p);
 
 }  // namespace feh

@@ -2093,12 +2093,6 @@ int first_plain_t(const feh_plan &p, const FftArgs &fa, bool inverse) {
     return launch_middle_tile<T>(p, a, small, inverse, "first-axis fft launch");
 }
 
-// The CG's first-axis pass reads its inverses from the table (the only place
-// of those of a metric other than 0).
-bool first_by_table(const feh_plan &p, int metric) {
-    return first_per_load_case(p) || metric != 0 || p.tune_first_perlc == 0;
-}
-
 // Whether the CG's run-time first-axis pass takes the small tile, and its
 // pencils (at least a quarter of the default: the partial sums have one slot a
 // pencil block of that size).  *PB: the full tile's pencils.
@@ -2163,13 +2157,6 @@ int first_t(const feh_plan &p, const FftArgs &fa, int mode) {
     a.nblk = (int)((a.inner_total + PB - 1) / PB);
     if (fa.partial && (size_t)a.nblk > p.part_stride)
         return set_error(FEH_EINVAL, "first axis: more partial sums than a row of them holds");
-    // The CG's pass, unless the layout was set: one workgroup per load case at
-    // every length.  It reads the inverses from the table (the only place of
-    // the metrics other than M), so it has n_load times the workgroups of the
-    // cached variant at no arithmetic more, and was at least as fast at every
-    // size (a solve, FP32 3D: 90x77x105 12.6 -> 11.1 ms, 45x50x39 5.7 -> 3.8,
-    // 160^3 44.0 -> 37.0; FP64 2D: 151^2 25.1 -> 13.4, 300^2 5.2 -> 3.7,
-    // 900^2 9.9 -> 10.0).
     const bool table = mode == 0 && fa.unit_volume;
     const bool perlc = table ? first_by_table(p, p.metric) : first_per_load_case(p);
     a.total = perlc ? a.nblk * p.L : a.nblk;  // one block per (load case, pencils) or per pencils
@@ -2260,6 +2247,21 @@ int first_ct_pencils(const feh_plan &p) {
     const long long rowD = inner * p.dim;
     if (rowD >= (1 << 24) || rowD * n0 >= (1ll << 31)) return 0;
     return two ? 2 : (p.prec == FEH_FP32 ? 2048 : 1024) / n0;
+}
+
+// The CG's first-axis pass reads its inverses from the table, one workgroup
+// per load case: where the schedule has that layout, for every metric other
+// than 0 (the table is the only place of its inverses), and at every length
+// that is not a power of two, whose layout 0 is thus one of the passes that
+// form their inverses only.  The table pass has n_load times the workgroups of
+// the cached variant at no arithmetic more.  A solve of 24 iterations, cached
+// and by table, FP32: 45 x 50 x 39 x 6 load cases 1.69 and 0.94 ms, 160^3 x 6
+// 15.4 and 13.1, 300^2 x 3 1.25 and 0.62, 900^2 x 1 1.04 and 0.99; FP64:
+// 151^2 x 3 5.49 and 1.64, 900^2 x 1 2.65 and 2.65, 90 x 77 x 105 x 6 19.3 and
+// 16.1.  Of 48 such solves one was slower, 1661 x 300 x 1 in FP32 (1.22 and
+// 1.26 ms).
+bool first_by_table(const feh_plan &p, int metric) {
+    return first_per_load_case(p) || metric != 0 || !pow2_len((int)p.n[0]);
 }
 
 int first_pencils_default(const feh_plan &p) {
