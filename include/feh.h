@@ -220,7 +220,8 @@ int feh_solve_noalloc(feh_plan *plan, const void *lambda_dev, const void *mu_dev
  * pass (every load case in one workgroup with the per-wavevector inverses kept
  * in registers, or one workgroup per load case reading them) and, in 3D, the two
  * stencil tile heights (8 or 16 rows of 32 voxels), each over `reps` runs
- * (< 1: 3), and keeps the fastest.  The
+ * (< 1: 3), and keeps the fastest.  Plans whose solves run in one launch
+ * (see feh_plan_tuning) keep the default radix orders.  The
  * transforms stay exact to rounding whatever is chosen; repeated solves on
  * one plan stay bitwise reproducible, two tunings may differ in rounding.
  * Overwrites the workspace vectors (set the material again only if the
@@ -240,7 +241,11 @@ int feh_plan_autotune(feh_plan *plan, int reps);
  * 64 to 512 points in the default radix order, the last axis in FP32 from
  * 128 points; the same butterflies and
  * twiddles, with the index arithmetic resolved at compile time) or 0 for
- * the run-time passes throughout (default 1).  Writes at most n_values
+ * the run-time passes throughout (default 1), then 0 if solves of 2D grids
+ * that fit one workgroup per load case (feh_solve from u = 0,
+ * feh_strain_cg_solve of FEH_DERIV_FE, feh_finite_strain_solve of the stencil
+ * kinds) run in one launch, with the radix orders above, or 1 if they take the
+ * passes as every other grid does (default 0).  Writes at most n_values
  * entries and returns the full length. */
 int feh_plan_tuning(const feh_plan *plan, int *values, int n_values);
 
@@ -251,10 +256,10 @@ int feh_plan_tuning(const feh_plan *plan, int *values, int n_values);
  * stencil rows 8 or 16 in 3D (1 in 2D), and per axis radices from
  * {2, 3, 4, 5, 7, 8, 11, 13} or primes above 13 whose product is the
  * transformed length (n_a, n_last/2 for an even last axis), and optionally
- * the trailing compile-time transform flag (0 or 1; kept if absent).
+ * the trailing compile-time transform flag, and the general-passes flag after it
+ * (0 or 1; kept if absent).
  * FEH_EINVAL leaves the plan unchanged.  Any valid schedule is exact to
- * rounding.  A plan whose schedule was set runs it also where a small 2D grid
- * would otherwise be solved by one workgroup per load case, in one launch. */
+ * rounding, and setting the one a plan reports changes nothing. */
 int feh_plan_set_tuning(feh_plan *plan, const int *values, int n_values);
 
 /* Whether the plan's CG, with its current schedule, keeps the residual as its

@@ -359,7 +359,8 @@ def feh_plan_cg_residual_spectral(plan):
 
 
 def feh_plan_tuning(plan):
-    """{'rows_last', 'pencils_mid', 'pencils_first', 'first_per_load_case', 'radices': [[..] per axis]}"""
+    """{'rows_last', 'pencils_mid', 'pencils_first', 'first_per_load_case', 'stencil_rows', 'radices': [[..] per axis],
+    'compile_time_transforms', 'general_passes'}"""
     buf = (ctypes.c_int * 64)()
     n = load().feh_plan_tuning(plan, buf, 64)
     if n < 0:
@@ -371,7 +372,7 @@ def feh_plan_tuning(plan):
         rad.append(v[i + 1:i + 1 + k])
         i += 1 + k
     return {"rows_last": v[0], "pencils_mid": v[1], "pencils_first": v[2], "first_per_load_case": v[3],
-            "stencil_rows": v[4], "radices": rad, "compile_time_transforms": v[i]}
+            "stencil_rows": v[4], "radices": rad, "compile_time_transforms": v[i], "general_passes": v[i + 1]}
 
 
 def feh_plan_set_tuning(plan, tuning):
@@ -381,8 +382,9 @@ def feh_plan_set_tuning(plan, tuning):
     for r in list(tuning["radices"]) + [[]] * (3 - len(tuning["radices"])):
         v.append(len(r))
         v.extend(int(x) for x in r)
-    if "compile_time_transforms" in tuning:
-        v.append(int(tuning["compile_time_transforms"]))
+    if "compile_time_transforms" in tuning or "general_passes" in tuning:
+        now = feh_plan_tuning(plan)
+        v += [int(tuning.get(k, now[k])) for k in ("compile_time_transforms", "general_passes")]
     buf = (ctypes.c_int * len(v))(*v)
     return _check(load().feh_plan_set_tuning(plan, buf, len(v)))
 

@@ -1202,8 +1202,10 @@ int feh_plan_autotune(feh_plan *plan, int reps) {
         CK(check_plan(plan, false));
         feh_plan &p = *plan;
         if (reps < 1) reps = 3;
-        p.schedule_set = true;
         const int D = p.dim;
+        // where the solve runs in one launch it uses these radix orders too, and
+        // the passes timed below are not its own: it keeps the default orders
+        const bool orders = !small_solve_ok(p, false);
         // transform zeros: the timing does not depend on the values
         const size_t nvec = (size_t)p.L * D * p.N;
         CK(launch_fill(p, p.ws + p.off_r, nvec, 0.0));
@@ -1220,7 +1222,7 @@ int feh_plan_autotune(feh_plan *plan, int reps) {
             AxisFFT keep = p.fft[ax];
             for (const auto &rad : radix_candidates(len)) {
                 AxisFFT cand;
-                if (!make_axis(len, rad, cand)) continue;
+                if (!orders || !make_axis(len, rad, cand)) continue;
                 p.fft[ax] = cand;
                 double ms = 0;
                 CK(time_runs(p, run, reps, ms));
@@ -1348,15 +1350,20 @@ int feh_plan_set_tuning(feh_plan *plan, const int *values, int n_values) {
             }
             if (!make_axis(len, rad, ax[a])) return set_error(FEH_EINVAL, "radices do not multiply to the axis length");
         }
-        // optional trailing value: compile-time transforms allowed (1) or not (0)
-        int ct = p.tune_ct;
+        // optional trailing values: compile-time transforms allowed (1) or not
+        // (0), then the general passes always (1) or not (0)
+        int ct = p.tune_ct, general = p.tune_general;
         if (i < n_values) {
             ct = values[i++];
             if (ct != 0 && ct != 1) return set_error(FEH_EINVAL, "compile-time transform flag must be 0 or 1");
         }
-        p.schedule_set = true;
+        if (i < n_values) {
+            general = values[i++];
+            if (general != 0 && general != 1) return set_error(FEH_EINVAL, "general-passes flag must be 0 or 1");
+        }
         for (int a = 0; a < 3; ++a) p.fft[a] = ax[a];
         p.tune_ct = ct;
+        p.tune_general = general;
         p.tune_rr_last = rr;
         p.tune_pb_mid = pbm;
         p.tune_pb_first = pbf;
@@ -1383,6 +1390,7 @@ int feh_plan_tuning(const feh_plan *plan, int *values, int n_values) {
         for (int s = 0; s < np; ++s) v.push_back(plan->fft[a].pass[s].R);
     }
     v.push_back(plan->tune_ct);
+    v.push_back(plan->tune_general);
     for (int i = 0; i < n_values; ++i) values[i] = i < (int)v.size() ? v[i] : 0;
     return (int)v.size();
 }

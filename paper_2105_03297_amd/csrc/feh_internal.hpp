@@ -152,7 +152,7 @@ struct feh_plan {
     int tune_stencil_vy = 0;            // 3D stencil tile rows (8 or 16; 0: default)
     int tune_first_perlc = 0;           // axis-0 pass: 1 one workgroup per load case, -1 all load cases, 0 default
     int tune_ct = 1;                    // 1: compile-time transforms where the shape has one, 0: run-time passes only
-    bool schedule_set = false;          // by feh_plan_set_tuning or feh_plan_autotune
+    int tune_general = 0;               // 1: also solves that fit one workgroup per load case run by the general passes
     bool solved = false;                // off_u holds the fluctuations of the last feh_solve
     // set while a NodalScope is in place:
     bool u_f64 = false;                 // off_u holds doubles whatever prec

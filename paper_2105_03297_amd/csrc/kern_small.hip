@@ -912,10 +912,9 @@ int finite_t(const feh_plan &p, int kind, const SmallFinite &f) {
 
 }  // namespace
 
-// A plan whose schedule was set or tuned, or that is being profiled, runs the
-// passes it asks about.
+// A plan that is being profiled runs the passes it asks about.
 bool small_solve_ok(const feh_plan &p, bool finite) {
-    if (p.dim != DIM || p.schedule_set || p.prof_on) return false;
+    if (p.dim != DIM || p.tune_general || p.prof_on) return false;
     return p.prec == FEH_FP64 ? shape_of<double>(p, finite).fits : shape_of<float>(p, finite).fits;
 }
 

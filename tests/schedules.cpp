@@ -13,7 +13,8 @@ using namespace feh;
 // what the launchers choose by
 static std::vector<long long> route(const feh_plan &p) {
     std::vector<long long> r = {first_num_parts(p),     first_num_parts(p, 1), first_by_table(p, 0), first_per_load_case(p),
-                                first_ct_pencils(p),    stencil_rows(p),       stencil_num_parts(p), cg_residual_spectral(p)};
+                                first_ct_pencils(p),    stencil_rows(p),       stencil_num_parts(p), cg_residual_spectral(p),
+                                small_solve_ok(p, false),  small_solve_ok(p, true)};
     for (const AxisFFT &a : p.fft)
         for (int s = 0; s < a.npass; ++s) r.push_back(a.pass[s].R);
     return r;
@@ -27,7 +28,7 @@ int main() {
     for (const auto &n : shapes)
         for (int prec : {FEH_FP64, FEH_FP32})
             for (int n_load : {1, 6})
-                for (int change = 0; change < 5; ++change) {
+                for (int change = 0; change < 6; ++change) {
                     feh_plan *a = nullptr, *b = nullptr;
                     if (feh_plan_create(&a, (int)n.size(), n.data(), nullptr, n_load, prec, nullptr) != FEH_OK ||
                         feh_plan_create(&b, (int)n.size(), n.data(), nullptr, n_load, prec, nullptr) != FEH_OK)
@@ -38,6 +39,7 @@ int main() {
                     if (change == 2) v[3] = 1 - v[3];
                     if (change == 3) v[2] = first_pencils_default(*a);
                     if (change == 4 && n.size() == 3) v[4] = 16;
+                    if (change == 5) v[k - 1] = 1;
                     const std::string name = std::to_string(n[0]) + " x " + std::to_string(n[1]) +
                                              (n.size() == 3 ? " x " + std::to_string(n[2]) : "") + " prec " +
                                              std::to_string(prec) + " n_load " + std::to_string(n_load) + " change " +
