@@ -1,5 +1,6 @@
 // Discrete derivative symbols of the strain-space solvers (small and finite
-// strain): the derivative kinds of Sec. "Discrete projection", their Fourier
+// strain): the derivative kinds of Sec. "Discrete projection" and, but for the
+// finite elements' (whose solvers run on nodal vectors), their Fourier
 // symbols D_T(k) per evaluation point T evaluated on the fly from the
 // wavevector index, and the small D x D Hermitian inverse of the small-strain
 // projection.  Shared by spectral.hip and finite.hip (internal linkage).
@@ -63,7 +64,7 @@ using C64 = Cx<double>;
 
 template <int DIM, int KIND>
 struct Pts {
-    static constexpr int NE = KIND == K_FE ? (DIM == 3 ? 6 : 2) : (KIND == K_FOURIER2 ? 2 : 1);
+    static constexpr int NE = KIND == K_FOURIER2 ? 2 : 1;
 };
 
 // Symbol D[T][a] at half-spectrum index k, normalised to sum |D|^2 = 1.
@@ -97,41 +98,7 @@ __device__ __forceinline__ bool symbol_at(const SymArgs &sa, long long k, C64 (&
         th[a] = M_PI * x;
         sincospi(x, &sn[a], &cs[a]);
     }
-    if constexpr (KIND == K_FE) {
-        // vertex phases e^{i k.r} of the voxel corners (bit a: +1 along axis a)
-        C64 P[1 << DIM];
-        #pragma unroll
-        for (int r = 0; r < (1 << DIM); ++r) {
-            C64 v{1.0, 0.0};
-            #pragma unroll
-            for (int a = 0; a < DIM; ++a)
-                if (r & (1 << a)) v = cmul(v, C64{cs[a], sn[a]});
-            P[r] = v;
-        }
-        // the gradient of a linear simplex along a voxel edge of its vertex
-        // path is the difference of the edge's end values over h_a: tetrahedron
-        // (A0, A1, A2) runs 0 -> e_A0 -> e_A0 + e_A1 -> (1,1,1); triangle 0 has
-        // edges 00-10 (x) and 00-01 (y), triangle 1 edges 01-11 (x) and 10-11 (y)
-        double ih[DIM];
-        #pragma unroll
-        for (int a = 0; a < DIM; ++a) ih[a] = 1.0 / sa.h[a];
-        if constexpr (DIM == 3) {
-            constexpr int perm[6][3] = {{0, 1, 2}, {0, 2, 1}, {1, 0, 2}, {1, 2, 0}, {2, 0, 1}, {2, 1, 0}};
-            #pragma unroll
-            for (int e = 0; e < 6; ++e) {
-                const int A0 = perm[e][0], A1 = perm[e][1], A2 = perm[e][2];
-                const int V1 = 1 << A0, V2 = V1 | (1 << A1);
-                D[e][A0] = cscale(csub(P[V1], P[0]), ih[A0]);
-                D[e][A1] = cscale(csub(P[V2], P[V1]), ih[A1]);
-                D[e][A2] = cscale(csub(P[7], P[V2]), ih[A2]);
-            }
-        } else {
-            D[0][0] = cscale(csub(P[1], P[0]), ih[0]);
-            D[0][1] = cscale(csub(P[2], P[0]), ih[1]);
-            D[1][0] = cscale(csub(P[3], P[2]), ih[0]);
-            D[1][1] = cscale(csub(P[3], P[1]), ih[1]);
-        }
-    } else if constexpr (KIND == K_FD) {
+    if constexpr (KIND == K_FD) {
         #pragma unroll
         for (int a = 0; a < DIM; ++a) D[0][a] = C64{(cs[a] - 1.0) / sa.h[a], sn[a] / sa.h[a]};
     } else if constexpr (KIND == K_CD) {
