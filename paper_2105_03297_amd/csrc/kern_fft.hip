@@ -216,7 +216,7 @@ __host__ __device__ inline int prime_tiles(int points, int R) {
 //   y_k = A_k -+ i B_k, y_{R-k} = A_k +- i B_k      (k = 0 .. H),
 // a quarter of the multiplications of the sum over all c, and two real
 // products of a table with the real and imaginary parts of every butterfly
-// as columns.  The direct sum (direct_pass, below) spends an LDS read of a
+// as columns.  The direct sum (direct_pass, above) spends an LDS read of a
 // twiddle for every few multiplications; here a lane reads one table entry
 // and two operands for 16 x 16 x 4 x 2 of them.  Measured, FP64 (with the small
 // tiles for the first): 151^2 Fourier strain-space solve 22.6 -> 3.3 ms; 1661^2

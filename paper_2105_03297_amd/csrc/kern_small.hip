@@ -1,5 +1,5 @@
 // Whole solves of 2D grids that fit one CU: one workgroup per load case keeps the
-// search direction, the spectrum, the spectral residual, u and, for finite
+// search direction, the spectrum, the residual, u and, for finite
 // strain, the displacement in LDS and runs the CG (or Newton with its CG) to
 // the end in one launch.
 //
@@ -10,11 +10,17 @@
 // solve, the transforms and M^-1, FP64 for every sum and for the finite-strain
 // stress.
 // Bound: LDS latency and barriers.
-// Measured against the general path (FP64): solve of 3 load cases to 1e-10,
-// 8^2 0.94 -> 0.24 ms, 17^2 1.24 -> 0.47, 32^2 1.70 -> 0.69, 46^2 2.00 -> 1.45;
-// finite strain, tolerances 1e-10, 17^2 2.9 -> 0.9 ms, 32^2 7.7 -> 3.4.  It is
-// the faster wherever it fits, so the rule is the LDS that a solve needs (up
-// to about 47^2 in FP64, 66^2 in FP32; finite strain 42^2 and 50^2).
+// Measured against the general path, random materials of contrast 10: solve of
+// 3 load cases to 1e-10 in FP64, 8^2 0.90 -> 0.23 ms, 17^2 1.52 -> 0.48,
+// 33^2 1.65 -> 0.99, 48^2 1.49 -> 0.89; to 1e-5 in FP32, 64^2 0.83 -> 0.62;
+// finite strain of one load case to 1e-8 in FP64, 17^2 3.34 -> 1.22,
+// 40^2 4.36 -> 2.07.  Over 152 solves of 1 to 64 load cases and 64 finite-strain
+// solves, squares to 64^2 and strips to 2 x 1021, it was 1.3 to 5.4 times as
+// fast wherever it fits, so the rule is what fits: the LDS, the points a thread
+// may hold in a pass and the matrix-core tiles of the prime passes (odd rows
+// take twice the room of even ones).  Largest squares, even and odd: FP64 48^2
+// and 33^2, FP32 64^2 and 47^2; finite strain FP64 40^2 and 33^2, FP32 50^2 and
+// 47^2.
 #include <algorithm>
 #include <cmath>
 #include <cstring>

@@ -41,7 +41,8 @@
 // with its vectors in the caller's buffer and u kept in double, so that the
 // strains differenced from it lose no digits that FP32 strains would have.
 // Measured, FP32 FE solve of 128^3 x 6 load cases to 1e-5: 277 -> 16 ms (20 iterations); FP64,
-// 1661^2, one load case to 1e-8: 160 -> 49 ms (its 151-point transforms bound both forms).
+// 1661^2, one load case to 1e-8: 160 -> 49 ms (17 with the prime passes and the tile sizes of
+// the first axis since; its 151-point transforms bound it).
 //
 // Layouts: real fields [L][C][N] with C = n_e * nsym components per voxel
 // (symmetric components xx, yy, (zz, yz, xz,) xy per point); spectra
